@@ -313,7 +313,10 @@ int cm_forces_backward_percell(cm_batch h, const float* y, const float* fbar,
 /*
  * Launch configuration of the batched kernels: waves (tiles) per workgroup
  * (1, 2, 4, 8) and persistent workgroups per compute unit (0 = one workgroup
- * per group of tiles, not persistent).  cm_autotune times one forward +
+ * per group of tiles, not persistent).  (1, 0), the default, leaves the
+ * wavefronts per tile to the library; every other shape runs one wavefront
+ * per tile.  Results are bitwise the same under every shape.
+ * cm_autotune times one forward +
  * backward evaluation -- the fused pass of cm_forces_and_backward where its
  * LDS fits, else cm_forces then cm_forces_backward -- for every candidate
  * that fits in LDS on `stream`, with the handle's data,

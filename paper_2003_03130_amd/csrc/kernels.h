@@ -108,6 +108,22 @@ size_t forward_lds_per_wave(int nloc);
 size_t backward_lds_per_wave(int nloc);
 size_t forward_backward_lds_per_wave(int nloc);
 
+// Passes with several wavefronts per tile (wide.hip).  wide_waves: how many
+// for a pass over r, or 0 for the one-wavefront passes, which keep the
+// launch shapes of cm_set_launch other than its default; lds: the pass's LDS
+// per tile in bytes, hvp: a Hessian-vector product alone.
+int wide_waves(const Range& r, const LaunchCfg& cfg, size_t lds, bool hvp);
+hipError_t launch_wide_forward(const DeviceTables& T, const Range& r, int K, const float* y,
+                               float* f, hipStream_t st, const PlateFwd& pl, bool check);
+hipError_t launch_wide_backward(const DeviceTables& T, const Range& r, int K, const float* y,
+                                const float* fbar, const double* ebar, float* ybar,
+                                hipStream_t st, const CellMask& mask, const PlateBwd& pl,
+                                bool grad);
+hipError_t launch_wide_forward_backward(const DeviceTables& T, const DeviceTables& Tb,
+                                        const Range& r, int K, const float* y, float* f,
+                                        const float* fbar, const double* ebar, float* ybar,
+                                        hipStream_t st, bool grad);
+
 // The two kernels of each pass, separately (for per-kernel timing).
 // With pl.plate set, the forward pass applies one plate-compression step
 // (see plate.h): it writes pl.y_next (and pl.force) instead of f, and the
