@@ -133,12 +133,14 @@ static int create_from(cm::Prepared& P, const cm::PrepOptions& po,
   // host tables built here are copied asynchronously: they live until the
   // stream synchronisation below
   std::vector<int32_t> shared_cell, orphan_off, orphan, slot_first, shared_first;
-  std::vector<int4> pc;
+  std::vector<int4> pc, rec, rec4;
+  std::vector<int32_t> more;
   std::vector<int2> nbk;
   {
     cm::TileDesc* tiles;
     cm::TetChunk* chunks;
-    int32_t *slot_node, *shared_node, *ssp, *ss, *ctf, *ctc, *tmat, *mtf, *mtc, *scell;
+    int4 *drec, *drec4;
+    int32_t *slot_node, *dmore, *ctf, *ctc, *tmat, *mtf, *mtc, *scell;
     int32_t *orph_off, *orph, *sfirst, *cso;
     int64_t* noff;
     // cell of every shared node; slot_node with bit 31 on the first slot of
@@ -165,12 +167,27 @@ static int create_from(cm::Prepared& P, const cm::PrepOptions& po,
         if (P.shared_slot_ptr[s] == P.shared_slot_ptr[s + 1])
           orphan[fill[shared_cell[s]]++] = P.shared_node[s];
     }
+    // the slots of every shared node (SharedSlots, finalize.h)
+    rec.resize(n_shr);
+    for (size_t s = 0; s < n_shr; ++s) {
+      const int32_t* q = P.shared_slots.data() + P.shared_slot_ptr[s];
+      const int n = P.shared_slot_ptr[s + 1] - P.shared_slot_ptr[s];
+      auto at = [&](int j) { return j < n ? q[j] : -1; };
+      rec[s] = make_int4(P.shared_node[s], at(0), at(1), at(2));
+      if (n <= 3) continue;
+      rec[s].w = -2 - (int)rec4.size();
+      rec4.push_back(make_int4(at(2), at(3), at(4), at(5)));
+      if (n <= 6) continue;
+      rec4.back().w = -2 - (int)more.size();
+      more.push_back(n - 5);
+      more.insert(more.end(), q + 5, q + n);
+    }
     if ((rc = h->upload(&tiles, P.tiles, stream)) ||
         (rc = h->upload(&chunks, P.chunks, stream)) ||
         (rc = h->upload(&slot_node, P.slot_node, stream)) ||
-        (rc = h->upload(&shared_node, P.shared_node, stream)) ||
-        (rc = h->upload(&ssp, P.shared_slot_ptr, stream)) ||
-        (rc = h->upload(&ss, P.shared_slots, stream)) ||
+        (rc = h->upload(&drec, rec, stream)) ||
+        (rc = h->upload(&drec4, rec4, stream)) ||
+        (rc = h->upload(&dmore, more, stream)) ||
         (rc = h->upload(&scell, shared_cell, stream)) ||
         (rc = h->upload(&sfirst, slot_first, stream)) ||
         (rc = h->upload(&orph_off, orphan_off, stream)) ||
@@ -197,9 +214,9 @@ static int create_from(cm::Prepared& P, const cm::PrepOptions& po,
     T.tiles = tiles;
     T.chunks = chunks;
     T.slot_node = slot_node;
-    T.shared_node = shared_node;
-    T.shared_slot_ptr = ssp;
-    T.shared_slots = ss;
+    T.shared_rec = drec;
+    T.shared_rec4 = drec4;
+    T.shared_more = dmore;
     T.shared_cell = scell;
     T.slot_node_first = sfirst;
     T.orphan_off = orph_off;

@@ -194,7 +194,8 @@ __global__ __launch_bounds__(256) void backward_finalize_kernel(BwdFinArgs a,
   const int64_t N = a.T.n_nodes;
   if (gid < a.r.shared_end - a.r.shared_begin) {
     const int s = a.r.shared_begin + (int)gid;
-    const int64_t g = a.T.shared_node[s];
+    const SharedSlots sl = shared_slots(a.T.shared_rec[s], a.T.shared_rec4);
+    const int64_t g = sl.node;
     if (!m.flags || m.flags[(int64_t)a.T.shared_cell[s] * m.stride] != 0.0) {
       // plate step: the node's values are loaded before the partial sums,
       // so that the two chains of loads overlap
@@ -209,7 +210,7 @@ __global__ __launch_bounds__(256) void backward_finalize_kernel(BwdFinArgs a,
         bot = (float)a.pl.plate[2 * c + 1];
         gw = plate_loss_weight(a.pl.F_meas, a.pl.F_target, a.pl.scale, c);
       }
-      const float3 sm = shared_sum(a.T, a.T.part, s);
+      const float3 sm = shared_sum(a.T, a.T.part, sl);
       if (a.pl.plate) {
         plate_node_adjoint(pz, lx, ly, lz, sm.x, sm.y, sm.z, top, bot, a.pl.k, a.pl.m, gw,
                            a.pl.lam, N, g);

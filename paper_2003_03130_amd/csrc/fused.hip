@@ -208,22 +208,14 @@ __global__ __launch_bounds__(256) void forward_backward_finalize_kernel(
       (int64_t)(b - cell_blocks - slot_blocks) * blockDim.x + threadIdx.x;
   if (gid >= a.r.shared_end - a.r.shared_begin) return;
   const int s = a.r.shared_begin + (int)gid;
-  const int64_t g = a.T.shared_node[s];
+  const SharedSlots sl = shared_slots(a.T.shared_rec[s], a.T.shared_rec4);
+  const int64_t g = sl.node;
   const int64_t N = a.T.n_nodes;
-  float fx = 0.f, fy = 0.f, fz = 0.f, bx = 0.f, by = 0.f, bz = 0.f;
-  for (int q = a.T.shared_slot_ptr[s]; q < a.T.shared_slot_ptr[s + 1]; ++q) {
-    const int64_t sl = a.T.shared_slots[q];
-    const float* pf = a.T.part + 3 * sl;
-    const float* pb = a.part_b + 3 * sl;
-    fx += pf[0];
-    fy += pf[1];
-    fz += pf[2];
-    bx += pb[0];
-    by += pb[1];
-    bz += pb[2];
-  }
-  a.f[g] = fx; a.f[N + g] = fy; a.f[2 * N + g] = fz;
-  a.ybar[g] = bx; a.ybar[N + g] = by; a.ybar[2 * N + g] = bz;
+  const float* const part[2] = {a.T.part, a.part_b};
+  float v[2][3];
+  shared_sums(sl, a.T.shared_more, part, v);
+  a.f[g] = v[0][0]; a.f[N + g] = v[0][1]; a.f[2 * N + g] = v[0][2];
+  a.ybar[g] = v[1][0]; a.ybar[N + g] = v[1][1]; a.ybar[2 * N + g] = v[1][2];
 }
 
 template <int W>

@@ -13,12 +13,15 @@ struct DeviceTables {
   const TileDesc* tiles = nullptr;
   const TetChunk* chunks = nullptr;
   const int32_t* slot_node = nullptr;
-  const int32_t* shared_node = nullptr;
-  const int32_t* shared_slot_ptr = nullptr;
-  const int32_t* shared_slots = nullptr;
+  // shared nodes and their slots, in tile order (SharedSlots, finalize.h):
+  // (node, slot 0, slot 1, slot 2) per shared node, further slots in
+  // shared_rec4, still further ones in shared_more
+  const int4* shared_rec = nullptr;
+  const int4* shared_rec4 = nullptr;
+  const int32_t* shared_more = nullptr;
   const int32_t* shared_cell = nullptr;  // cell of every shared node
   const int32_t* cell_shared_off = nullptr;  // shared nodes of cell c: [off[c], off[c + 1])
-  const int32_t* cell_shared_first = nullptr;  // node id of shared_node[off[c]]
+  const int32_t* cell_shared_first = nullptr;  // id of cell c's first shared node
   // slot_node with bit 31 set on the first slot of every shared node (the
   // one slot whose tile adds the node's top-plate force to its sum)
   const int32_t* slot_node_first = nullptr;

@@ -202,7 +202,8 @@ __global__ __launch_bounds__(256) void forward_finalize_kernel(FinArgs a,
   const int64_t gid = (int64_t)(blockIdx.x - cell_blocks) * blockDim.x + threadIdx.x;
   if (gid < a.r.shared_end - a.r.shared_begin) {
     const int s = a.r.shared_begin + (int)gid;
-    const int64_t g = a.T.shared_node[s];
+    const SharedSlots sl = shared_slots(a.T.shared_rec[s], a.T.shared_rec4);
+    const int64_t g = sl.node;
     // plate step: the node's position and plates are loaded before the
     // partial sums, so that the two chains of loads overlap
     float px = 0.f, py = 0.f, pz = 0.f, top = 0.f, bot = 0.f;
@@ -214,7 +215,7 @@ __global__ __launch_bounds__(256) void forward_finalize_kernel(FinArgs a,
       top = (float)a.pl.plate[2 * c];
       bot = (float)a.pl.plate[2 * c + 1];
     }
-    const float3 sm = shared_sum(a.T, a.T.part, s);
+    const float3 sm = shared_sum(a.T, a.T.part, sl);
     if (a.pl.plate) {
       plate_node_step(px, py, pz, sm.x, sm.y, sm.z, top, bot, a.pl.k, a.pl.m, a.pl.y_next,
                       N, g);

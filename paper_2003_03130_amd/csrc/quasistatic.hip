@@ -16,6 +16,7 @@
 
 #include "aux_kernels.h"
 #include "device_util.h"
+#include "finalize.h"
 #include "kernels.h"
 
 namespace cm {
@@ -474,8 +475,9 @@ struct CgArgs {
   // without its finalize) and the shared nodes' values are the sums of
   // their slot partials, formed here in the finalize's order.
   const float* part;
-  const int32_t* shared_slot_ptr;
-  const int32_t* shared_slots;
+  const int4* shared_rec;
+  const int4* shared_rec4;
+  const int32_t* shared_more;
   const int32_t* cell_shared_off;
   const int32_t* cell_shared_first;  // first shared node of every cell
   Indenter ind;
@@ -507,14 +509,10 @@ __device__ __forceinline__ void ybar_of(const CgArgs& a, const ShrRange& sr, int
                                         float& bx, float& by, float& bz) {
   if (i >= sr.sh0 && i < sr.sh1) {
     const int s = sr.s0 + (int)(i - sr.sh0);
-    float sx = 0.f, sy = 0.f, sz = 0.f;
-    for (int q = a.shared_slot_ptr[s]; q < a.shared_slot_ptr[s + 1]; ++q) {
-      const float* pp = a.part + 3 * (int64_t)a.shared_slots[q];
-      sx += pp[0];
-      sy += pp[1];
-      sz += pp[2];
-    }
-    bx = sx; by = sy; bz = sz;
+    const float* const part[1] = {a.part};
+    float v[1][3];
+    shared_sums(shared_slots(a.shared_rec[s], a.shared_rec4), a.shared_more, part, v);
+    bx = v[0][0]; by = v[0][1]; bz = v[0][2];
   } else {
     bx = a.ybar[i]; by = a.ybar[a.N + i]; bz = a.ybar[2 * a.N + i];
   }
@@ -538,29 +536,25 @@ __device__ __forceinline__ void cg_finish(const CgArgs& a, double* s, double rn,
 // The iteration of qs_cg_kernel for a cell of at most R * kThreads nodes: p,
 // r, x, Hess(Pi) p and the preconditioner block of every node are loaded
 // once and kept in registers through the three phases (Ap is not stored).
-// The loads come in three waves, each issued whole before any of its
-// results is used: the node values with the slot ranges of the shared
-// nodes, then the ids of their first FS slots (most shared nodes have 2 or
-// 3; the others finish in a loop), then those slots' partials, summed in
-// slot order as the finalize does.  Same operations in the same order as
+// The loads come in two waves, each issued whole before any of its results
+// is used: the node values with the slot records of the shared nodes, then
+// those slots' partials, summed in slot order as the finalize does.  Same operations in the same order as
 // the streaming version (which fused multiply-adds the compiler forms may
 // differ between the two, a last-bit difference).
 template <int R, bool SPH>
 __device__ void cg_step_regs(const CgArgs& a, double* s, int c, int64_t n0, int64_t n1,
                              double top, double bot, double* red, const ShrRange& sr) {
   constexpr int kRegNodes = R;
-  constexpr int kFastSlots = R <= 2 ? 4 : 2;
   const int64_t N = a.N;
   float p[kRegNodes][3], r[kRegNodes][3], ap[kRegNodes][3], x[kRegNodes][3];
   float m[kRegNodes][6], b[kRegNodes][3];
   double h[kRegNodes];        // plates: penalty Hessian on zz
   float yv[kRegNodes][3];     // sphere: positions
-  int q0[kRegNodes], nq[kRegNodes];
+  int4 rec[kRegNodes];        // a shared node's slots (node < 0: an owned node)
 #pragma unroll
   for (int u = 0; u < kRegNodes; ++u) {
     const int64_t i = n0 + threadIdx.x + (int64_t)u * kThreads;
-    nq[u] = 0;
-    q0[u] = 0;
+    rec[u] = make_int4(-1, -1, -1, -1);
     if (i < n1) {
 #pragma unroll
       for (int d = 0; d < 3; ++d) {
@@ -580,10 +574,7 @@ __device__ void cg_step_regs(const CgArgs& a, double* s, int c, int64_t n0, int6
         h[u] = 2.0 * a.k * (fmax(z - top, 0.0) + fmax(bot - z, 0.0));
       }
       if (i >= sr.sh0 && i < sr.sh1) {
-        const int sn = sr.s0 + (int)(i - sr.sh0);
-        q0[u] = a.shared_slot_ptr[sn];
-        nq[u] = a.shared_slot_ptr[sn + 1] - q0[u];
-        b[u][0] = b[u][1] = b[u][2] = 0.f;
+        rec[u] = a.shared_rec[sr.s0 + (int)(i - sr.sh0)];
       } else {
         b[u][0] = a.ybar[i];
         b[u][1] = a.ybar[N + i];
@@ -591,28 +582,14 @@ __device__ void cg_step_regs(const CgArgs& a, double* s, int c, int64_t n0, int6
       }
     }
   }
-  int sl[kRegNodes][kFastSlots];
-#pragma unroll
-  for (int u = 0; u < kRegNodes; ++u)
-#pragma unroll
-    for (int j = 0; j < kFastSlots; ++j)
-      sl[u][j] = j < nq[u] ? a.shared_slots[q0[u] + j] : 0;
 #pragma unroll
   for (int u = 0; u < kRegNodes; ++u) {
+    if (rec[u].x >= 0) {
+      const float* const part[1] = {a.part};
+      float v[1][3];
+      shared_sums(shared_slots(rec[u], a.shared_rec4), a.shared_more, part, v);
 #pragma unroll
-    for (int j = 0; j < kFastSlots; ++j) {
-      if (j < nq[u]) {
-        const float* pp = a.part + 3 * (int64_t)sl[u][j];
-        b[u][0] += pp[0];
-        b[u][1] += pp[1];
-        b[u][2] += pp[2];
-      }
-    }
-    for (int j = kFastSlots; j < nq[u]; ++j) {
-      const float* pp = a.part + 3 * (int64_t)a.shared_slots[q0[u] + j];
-      b[u][0] += pp[0];
-      b[u][1] += pp[1];
-      b[u][2] += pp[2];
+      for (int c = 0; c < 3; ++c) b[u][c] = v[0][c];
     }
   }
   // sphere: centroid and sum (dx^2 + dy^2) of the Newton step's positions
@@ -1293,8 +1270,9 @@ hipError_t launch_qs_cg(const int64_t* node_off, int64_t N, int32_t n_cells,
                         hipStream_t s, const DeviceTables* slots, const Indenter& ind) {
   CgArgs a{node_off, N, y, plate, k, rel_tol, ybar, x, r, p, Ap, st, minv,
            slots ? slots->part : nullptr,
-           slots ? slots->shared_slot_ptr : nullptr,
-           slots ? slots->shared_slots : nullptr,
+           slots ? slots->shared_rec : nullptr,
+           slots ? slots->shared_rec4 : nullptr,
+           slots ? slots->shared_more : nullptr,
            slots ? slots->cell_shared_off : nullptr,
            slots ? slots->cell_shared_first : nullptr, ind};
   if (ind.R > 0.0)
