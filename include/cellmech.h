@@ -191,6 +191,15 @@ int cm_permutation(cm_batch h, int64_t* new_to_old);
  */
 int cm_set_params(cm_batch h, const double* mu, const double* kappa,
                   const double* w, int on_device, hipStream_t stream);
+/*
+ * cm_set_params_strided: cm_set_params with on_device = 1 from arrays on the
+ * handle's GPU with a stride (>= 0, in float64 elements) between the values
+ * of consecutive material slots, e.g. the columns of a (slots, 3) array; one
+ * kernel launch.  Errors as cm_set_params.
+ */
+int cm_set_params_strided(cm_batch h, const double* mu, int64_t stride_mu,
+                          const double* kappa, int64_t stride_kappa,
+                          const double* w, int64_t stride_w, hipStream_t stream);
 
 /*
  * cm_forces: forces and energies for all cells (eqs. elastic-force-vertex-0

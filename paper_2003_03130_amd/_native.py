@@ -72,6 +72,7 @@ SIGNATURES = {
     "cm_get_info": (_int, [_vp, ctypes.POINTER(Info)]),
     "cm_permutation": (_int, [_vp, _vp]),
     "cm_set_params": (_int, [_vp, _vp, _vp, _vp, _int, _vp]),
+    "cm_set_params_strided": (_int, [_vp, _vp, _i64, _vp, _i64, _vp, _i64, _vp]),
     "cm_forces": (_int, [_vp, _vp, _vp, _vp, _vp, _vp]),
     "cm_forces_noalloc": (_int, [_vp, _vp, _vp, _vp, _vp, _vp]),
     "cm_forces_checked": (_int, [_vp, _vp, _vp, _vp, _vp, _vp, _vp]),

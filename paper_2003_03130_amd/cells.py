@@ -210,13 +210,15 @@ class CellBatch:
         broadcast."""
         import torch
         if isinstance(mu, torch.Tensor):
-            tens = [t.to(self.device, torch.float64).contiguous().reshape(-1)
-                    for t in (mu, kappa, w)]
+            # one launch reads any 1-D tensors in place (columns of a
+            # (n_mat, 3) theta need no copy)
+            tens = [t.to(self.device, torch.float64) for t in (mu, kappa, w)]
+            tens = [t if t.dim() == 1 else t.contiguous().reshape(-1) for t in tens]
             if any(t.numel() != self.n_mat for t in tens):
                 raise ValueError(f"need {self.n_mat} values per parameter")
             self._param_keep = tens
-            nat.check(nat.lib().cm_set_params(
-                self._h, _ptr(tens[0]), _ptr(tens[1]), _ptr(tens[2]), 1,
+            nat.check(nat.lib().cm_set_params_strided(
+                self._h, *[v for t in tens for v in (_ptr(t), t.stride(0))],
                 _stream(stream)))
         else:
             arr = []
