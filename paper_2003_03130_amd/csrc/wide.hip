@@ -33,21 +33,83 @@
 namespace cm {
 namespace {
 
+// What the pass reads before its first tetrahedron comes first: the kernel
+// loads it with the arguments' first two cache lines.
 struct WideArgs {
-  DeviceTables T;  // part, tile_acc, tile_ninv, ...: the forward's scratch
-  Range r;
+  const TileDesc* tiles;
+  const TetChunk* chunks;
+  const int32_t* ids;      // slot_node, or slot_node_first for a plate step
+  const int32_t* tile_mat;
+  const double* params;
   const float* y;
+  const float* fbar;       // y where there is none (then has_fbar is 0)
+  const double* flags;     // per cell: CellMask (nullable)
+  int64_t flag_stride, N;
+  int32_t tile_begin, n_tiles, nloc, n_mat, last_slot, has_fbar;
+  int32_t check;           // count tets with a non-finite energy or force
+  const double* ebar;      // nullable
   float* f;
-  const float* fbar;    // nullable
-  const double* ebar;   // nullable
   float* ybar;
-  float* part_b;        // the backward's scratch
+  float* part;             // the forward's scratch
+  double* tile_acc;
+  double* tile_plate;
+  int32_t* tile_ninv;
+  int32_t* tile_nonfin;
+  float* part_b;           // the backward's
   double* tile_acc_b;
-  CellMask mask;
-  PlateFwd pf;          // used when PL and FWD
-  PlateBwd pb;          // used when PL and BWD
-  int check;            // count tets with a non-finite energy or force
+  PlateFwd pf;             // used when PL and FWD
+  PlateBwd pb;             // used when PL and BWD
 };
+
+WideArgs wide_args(const DeviceTables& T, const Range& r, const float* y,
+                   const int32_t* ids) {
+  WideArgs a{};
+  a.tiles = T.tiles;
+  a.chunks = T.chunks;
+  a.ids = ids;
+  a.tile_mat = T.tile_mat;
+  a.params = T.params;
+  a.y = y;
+  a.fbar = y;
+  a.flag_stride = 1;
+  a.N = T.n_nodes;
+  a.tile_begin = r.tile_begin;
+  a.n_tiles = r.tile_end - r.tile_begin;
+  a.nloc = T.nloc;
+  a.n_mat = T.n_mat;
+  a.last_slot = T.n_slots > 0 ? (int32_t)T.n_slots - 1 : 0;
+  return a;
+}
+
+// Loads grouped by data flow: each of these empty statements makes all of its
+// values available at once, so that the compiler issues their loads together
+// instead of each where its value is first used, one more round trip to
+// memory for every step.
+__device__ __forceinline__ void together(int32_t (&v)[2]) {
+  asm("" : "+v"(v[0]), "+v"(v[1]));
+}
+__device__ __forceinline__ void together(int32_t (&v)[3]) {
+  asm("" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]));
+}
+__device__ __forceinline__ void together(float (&v)[2][3]) {
+  asm("" : "+v"(v[0][0]), "+v"(v[0][1]), "+v"(v[0][2]), "+v"(v[1][0]), "+v"(v[1][1]),
+           "+v"(v[1][2]));
+}
+__device__ __forceinline__ void together(float (&v)[3][3]) {
+  asm("" : "+v"(v[0][0]), "+v"(v[0][1]), "+v"(v[0][2]), "+v"(v[1][0]), "+v"(v[1][1]),
+           "+v"(v[1][2]), "+v"(v[2][0]), "+v"(v[2][1]), "+v"(v[2][2]));
+}
+__device__ __forceinline__ void together(float (&v)[2][3], float (&w)[2][3]) {
+  asm("" : "+v"(v[0][0]), "+v"(v[0][1]), "+v"(v[0][2]), "+v"(v[1][0]), "+v"(v[1][1]),
+           "+v"(v[1][2]), "+v"(w[0][0]), "+v"(w[0][1]), "+v"(w[0][2]), "+v"(w[1][0]),
+           "+v"(w[1][1]), "+v"(w[1][2]));
+}
+__device__ __forceinline__ void together(float (&v)[3][3], float (&w)[3][3]) {
+  asm("" : "+v"(v[0][0]), "+v"(v[0][1]), "+v"(v[0][2]), "+v"(v[1][0]), "+v"(v[1][1]),
+           "+v"(v[1][2]), "+v"(v[2][0]), "+v"(v[2][1]), "+v"(v[2][2]), "+v"(w[0][0]),
+           "+v"(w[0][1]), "+v"(w[0][2]), "+v"(w[1][0]), "+v"(w[1][1]), "+v"(w[1][2]),
+           "+v"(w[2][0]), "+v"(w[2][1]), "+v"(w[2][2]));
+}
 
 // LDS of a workgroup, in the order of the kernel's carve-up (every part a
 // multiple of 16 bytes: nloc is a multiple of 4).
@@ -88,12 +150,17 @@ __global__ __launch_bounds__(64 * K) void wide_kernel(WideArgs a) {
   extern __shared__ float4 lds[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int nloc = a.T.nloc;
-  const int64_t N = a.T.n_nodes;
+  const int nloc = a.nloc, nm = a.n_mat;
+  const int64_t N = a.N;
+  // the arguments of the prologue in one round trip
+  asm("" : "+s"(a.tile_begin)
+      : "s"(a.tiles), "s"(a.chunks), "s"(a.ids), "s"(a.tile_mat), "s"(a.params), "s"(a.y),
+        "s"(a.N), "s"(a.last_slot));
+  if constexpr (BWD) asm("" : "+s"(a.tile_begin) : "s"(a.fbar), "s"(a.flags));
 
-  const int t = a.r.tile_begin + xcd_block(blockIdx.x, gridDim.x);
-  const TileDesc d = a.T.tiles[t];
-  if (a.mask.flags && a.mask.flags[(int64_t)d.cell * a.mask.stride] == 0.0) return;
+  const int t = a.tile_begin + xcd_block(blockIdx.x, a.n_tiles);
+  TileDesc d = a.tiles[t];
+  int mt = a.tile_mat[t];
   // (y.x, y.y, y.z, fbar.x or the plate step's flag) as float4, (fbar.y,
   // fbar.z) as float2, force and ybar sums as packed float3, per lane the
   // energy sum and the sums of V0 gp and V0 ge (three each)
@@ -119,31 +186,10 @@ __global__ __launch_bounds__(64 * K) void wide_kernel(WideArgs a) {
   int* cnt = reinterpret_cast<int*>(at);  // per wave: inverted, non-finite
   int* turn = cnt + 2 * K;                // the chunk whose turn it is
 
-  // the first chunk's loads go out before the node gather
-  TetRegs cur{};
-  if (wave < d.n_chunks) load_tet(a.T.chunks + d.chunk_begin + wave, lane, cur);
-  const int mt = a.T.tile_mat[t], nm = a.T.n_mat;
-  const bool has_fbar = BWD && a.fbar != nullptr;
-  const int nl = d.n_own + d.n_shr;
-  for (int l = tid; l < nl; l += 64 * K) {
-    int64_t g;
-    float w = 0.f;
-    if constexpr (PL && FWD) {
-      const int32_t v = l < d.n_own ? INT32_MIN | (d.own_begin + l)
-                                    : a.T.slot_node_first[d.shr_begin + l - d.n_own];
-      g = v & 0x7fffffff;
-      w = v < 0 ? 1.f : 0.f;
-    } else {
-      g = l < d.n_own ? (int64_t)d.own_begin + l
-                      : (int64_t)a.T.slot_node[d.shr_begin + l - d.n_own];
-    }
-    if constexpr (BWD) {
-      if (has_fbar) w = a.fbar[g];
-      vs[l] = has_fbar ? make_float2(a.fbar[N + g], a.fbar[2 * N + g]) : make_float2(0.f, 0.f);
-      gs[3 * l] = 0.f; gs[3 * l + 1] = 0.f; gs[3 * l + 2] = 0.f;
-    }
-    if constexpr (FWD) { fs[3 * l] = 0.f; fs[3 * l + 1] = 0.f; fs[3 * l + 2] = 0.f; }
-    ys[l] = make_float4(a.y[g], a.y[N + g], a.y[2 * N + g], w);
+  // the sums start at zero, while the descriptor is on its way
+  for (int i = tid; i < 3 * nloc / 4; i += 64 * K) {
+    if constexpr (FWD) reinterpret_cast<float4*>(fs)[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if constexpr (BWD) reinterpret_cast<float4*>(gs)[i] = make_float4(0.f, 0.f, 0.f, 0.f);
   }
   if (tid < 64) {
     if constexpr (FWD) el[tid] = 0.0;
@@ -153,9 +199,59 @@ __global__ __launch_bounds__(64 * K) void wide_kernel(WideArgs a) {
     }
   }
   if (tid == 0) *turn = 0;
-  const double mu = a.T.params[mt];
-  const double kappa = a.T.params[nm + mt];
-  const double w = a.T.params[2 * nm + mt];
+  asm("" : "+s"(d.chunk_begin), "+s"(d.n_own), "+s"(mt));
+  if (BWD && a.flags && a.flags[(int64_t)d.cell * a.flag_stride] == 0.0) return;
+
+  // the first chunk's loads go out before the node gather
+  TetRegs cur{};
+  if (wave < d.n_chunks) load_tet(a.chunks + d.chunk_begin + wave, lane, cur);
+  const int nl = d.n_own + d.n_shr;
+  // Node gather: the ids of U nodes per thread, then their positions and
+  // cotangents, each step's loads issued together (a loop over single nodes
+  // waits for both steps every time, and a tile of 283 nodes makes two or
+  // three rounds of 64 K threads).  Threads past the last node load a valid
+  // one again.
+  constexpr int U = K == 4 ? 2 : 3;
+  double mu = a.params[mt], kappa = a.params[nm + mt], w = a.params[2 * nm + mt];
+  for (int b = 0; b < nl; b += U * 64 * K) {
+    const int l0 = b + tid;
+    int32_t v[U];
+    float yv[U][3], fv[U][3];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      v[u] = a.ids[min(d.shr_begin + max(min(l0 + u * 64 * K, nl - 1) - d.n_own, 0),
+                       a.last_slot)];
+    together(v);
+    // (the material has arrived when the first addresses are formed)
+    asm("" : "+s"(mu), "+s"(kappa), "+s"(w), "+s"(d.own_begin));
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int l = min(l0 + u * 64 * K, nl - 1);
+      if (l < d.n_own) v[u] = (PL && FWD ? INT32_MIN : 0) | (d.own_begin + l);
+      const int64_t g = v[u] & 0x7fffffff;
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        yv[u][c] = a.y[c * N + g];
+        if constexpr (BWD) fv[u][c] = a.fbar[c * N + g];
+      }
+    }
+    if constexpr (BWD)
+      together(yv, fv);
+    else
+      together(yv);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int l = l0 + u * 64 * K;
+      if (l < nl) {
+        float f0 = PL && FWD && v[u] < 0 ? 1.f : 0.f;
+        if constexpr (BWD) {
+          f0 = a.has_fbar ? fv[u][0] : 0.f;
+          vs[l] = a.has_fbar ? make_float2(fv[u][1], fv[u][2]) : make_float2(0.f, 0.f);
+        }
+        ys[l] = make_float4(yv[u][0], yv[u][1], yv[u][2], f0);
+      }
+    }
+  }
   const Material mat{w * mu, (1.0 - w) * mu, kappa};
   const double eb = (GRAD && a.ebar) ? a.ebar[d.cell] : 0.0;
   float top = 0.f, bot = 0.f, gw = 0.f;
@@ -211,7 +307,7 @@ __global__ __launch_bounds__(64 * K) void wide_kernel(WideArgs a) {
       ninv += __popcll(__ballot(inv));
       if (!BWD && a.check) nonfin += __popcll(__ballot(bad));
     }
-    if (k + K < d.n_chunks) load_tet(a.T.chunks + d.chunk_begin + k + K, lane, cur);
+    if (k + K < d.n_chunks) load_tet(a.chunks + d.chunk_begin + k + K, lane, cur);
     // this chunk's turn: the chunks before it have been added
     // byte offsets of the four vertices' sums, and the sums that slot 3 takes
     // the negative of
@@ -297,7 +393,7 @@ __global__ __launch_bounds__(64 * K) void wide_kernel(WideArgs a) {
     } else {
       const int64_t s = 3 * ((int64_t)d.shr_begin + l - d.n_own);
       if constexpr (FWD) {
-        a.T.part[s] = fv[0]; a.T.part[s + 1] = fv[1]; a.T.part[s + 2] = fv[2];
+        a.part[s] = fv[0]; a.part[s + 1] = fv[1]; a.part[s + 2] = fv[2];
       }
       if constexpr (BWD) {
         a.part_b[s] = gv[0]; a.part_b[s + 1] = gv[1]; a.part_b[s + 2] = gv[2];
@@ -321,7 +417,7 @@ __global__ __launch_bounds__(64 * K) void wide_kernel(WideArgs a) {
           if (p.w != 0.f) fp += plate_top_term(p.z, top, a.pf.k);
         }
         fp = wave_sum(fp);
-        if (lane == 0) a.T.tile_plate[t] = fp;
+        if (lane == 0) a.tile_plate[t] = fp;
       }
       if (lane == 0) {
         int ni = 0, nf = 0;
@@ -330,9 +426,9 @@ __global__ __launch_bounds__(64 * K) void wide_kernel(WideArgs a) {
           ni += cnt[2 * k];
           nf += cnt[2 * k + 1];
         }
-        a.T.tile_acc[t] = eacc;
-        a.T.tile_ninv[t] = ni;
-        if (!BWD && a.check) a.T.tile_nonfin[t] = nf;
+        a.tile_acc[t] = eacc;
+        a.tile_ninv[t] = ni;
+        if (!BWD && a.check) a.tile_nonfin[t] = nf;
       }
     }
   }
@@ -340,9 +436,8 @@ __global__ __launch_bounds__(64 * K) void wide_kernel(WideArgs a) {
 
 template <int K, bool FWD, bool BWD, bool PL, bool GRAD>
 hipError_t wide_go(const WideArgs& a, hipStream_t st) {
-  const int grid = a.r.tile_end - a.r.tile_begin;
-  hipLaunchKernelGGL((wide_kernel<K, FWD, BWD, PL, GRAD>), dim3(grid), dim3(64 * K),
-                     (wide_lds<K, FWD, BWD, GRAD>(a.T.nloc)), st, a);
+  hipLaunchKernelGGL((wide_kernel<K, FWD, BWD, PL, GRAD>), dim3(a.n_tiles), dim3(64 * K),
+                     (wide_lds<K, FWD, BWD, GRAD>(a.nloc)), st, a);
   return hipGetLastError();
 }
 
@@ -371,8 +466,15 @@ int wide_waves(const Range& r, const LaunchCfg& cfg, size_t lds, bool hvp) {
 
 hipError_t launch_wide_forward(const DeviceTables& T, const Range& r, int K, const float* y,
                                float* f, hipStream_t st, const PlateFwd& pl, bool check) {
-  WideArgs a{T, r, y, f, nullptr, nullptr, nullptr, nullptr, nullptr, CellMask{}, pl,
-             PlateBwd{}, check ? 1 : 0};
+  WideArgs a = wide_args(T, r, y, pl.plate ? T.slot_node_first : T.slot_node);
+  a.f = f;
+  a.part = T.part;
+  a.tile_acc = T.tile_acc;
+  a.tile_plate = T.tile_plate;
+  a.tile_ninv = T.tile_ninv;
+  a.tile_nonfin = T.tile_nonfin;
+  a.check = check ? 1 : 0;
+  a.pf = pl;
   return pl.plate ? wide_k<true, false, true, false>(K, a, st)
                   : wide_k<true, false, false, false>(K, a, st);
 }
@@ -381,7 +483,16 @@ hipError_t launch_wide_backward(const DeviceTables& T, const Range& r, int K, co
                                 const float* fbar, const double* ebar, float* ybar,
                                 hipStream_t st, const CellMask& mask, const PlateBwd& pl,
                                 bool grad) {
-  WideArgs a{T, r, y, nullptr, fbar, ebar, ybar, T.part, T.tile_acc, mask, PlateFwd{}, pl, 0};
+  WideArgs a = wide_args(T, r, y, T.slot_node);
+  if (fbar) a.fbar = fbar;
+  a.has_fbar = fbar ? 1 : 0;
+  a.ebar = ebar;
+  a.ybar = ybar;
+  a.part_b = T.part;
+  a.tile_acc_b = T.tile_acc;
+  a.flags = mask.flags;
+  a.flag_stride = mask.stride;
+  a.pb = pl;
   if (pl.plate)
     return grad ? wide_k<false, true, true, true>(K, a, st)
                 : wide_k<false, true, true, false>(K, a, st);
@@ -393,8 +504,17 @@ hipError_t launch_wide_forward_backward(const DeviceTables& T, const DeviceTable
                                         const Range& r, int K, const float* y, float* f,
                                         const float* fbar, const double* ebar, float* ybar,
                                         hipStream_t st, bool grad) {
-  WideArgs a{T, r, y, f, fbar, ebar, ybar, Tb.part, Tb.tile_acc, CellMask{}, PlateFwd{},
-             PlateBwd{}, 0};
+  WideArgs a = wide_args(T, r, y, T.slot_node);
+  a.f = f;
+  a.part = T.part;
+  a.tile_acc = T.tile_acc;
+  a.tile_ninv = T.tile_ninv;
+  if (fbar) a.fbar = fbar;
+  a.has_fbar = fbar ? 1 : 0;
+  a.ebar = ebar;
+  a.ybar = ybar;
+  a.part_b = Tb.part;
+  a.tile_acc_b = Tb.tile_acc;
   return grad ? wide_k<true, true, false, true>(K, a, st)
               : wide_k<true, true, false, false>(K, a, st);
 }
