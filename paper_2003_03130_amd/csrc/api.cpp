@@ -135,6 +135,7 @@ static int create_from(cm::Prepared& P, const cm::PrepOptions& po,
   std::vector<int32_t> shared_cell, orphan_off, orphan, slot_first, shared_first;
   std::vector<int4> pc, rec, rec4;
   std::vector<int32_t> more;
+  cm::ListHost lists;
   std::vector<int2> nbk;
   {
     cm::TileDesc* tiles;
@@ -240,6 +241,13 @@ static int create_from(cm::Prepared& P, const cm::PrepOptions& po,
         (rc = h->alloc(&tile_plate, (size_t)h->n_tiles)) ||
         (rc = h->alloc(&tile_ninv, (size_t)h->n_tiles)))
       return bail(rc);
+    // node lists, for the few tiles with which their passes are the faster
+    if (h->n_tiles <= cm::list_tiles() && cm::list_tables(P, &lists)) {
+      uint16_t* blocks;
+      if ((rc = h->upload(&blocks, lists.blocks, stream))) return bail(rc);
+      T.lists = cm::ListTables{reinterpret_cast<const uint4*>(blocks), lists.stride16,
+                               lists.chunks, lists.groups};
+    }
     // 256 x 256 node-pair blocks of every cell (row block <= column block);
     // the cell's nodes are ordered candidates first, so the pairs of the
     // first ceil(candidates / 256) blocks hold every candidate pair

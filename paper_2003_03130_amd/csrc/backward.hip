@@ -250,6 +250,8 @@ hipError_t launch_backward_main(const DeviceTables& T, const Range& r,
   // the per-wave LDS stride (10 nloc / 4 float4) needs nloc % 4 == 0, else
   // a wave's last float2 would overlap the next wave's records
   if (T.nloc <= 0 || T.nloc % 4 != 0) return hipErrorInvalidValue;
+  if (use_lists(T, r, cfg, false, true, grad))
+    return launch_list_backward(T, r, y, fbar, ebar, ybar, st, mask, pl, grad);
   if (const int K = wide_waves(r, cfg, backward_lds_per_wave(T.nloc), !grad))
     return launch_wide_backward(T, r, K, y, fbar, ebar, ybar, st, mask, pl, grad);
   BwdArgs a{T, r, y, fbar, ebar, ybar, mask, pl};

@@ -243,6 +243,8 @@ hipError_t launch_forward_backward_main(const DeviceTables& T, const DeviceTable
   // LDS strides need it; this pass's 48-byte stride keeps its float4
   // records aligned for any nloc)
   if (T.nloc <= 0 || T.nloc % 4 != 0) return hipErrorInvalidValue;
+  if (use_lists(T, r, cfg, true, true, grad))
+    return launch_list_forward_backward(T, Tb, r, y, f, fbar, ebar, ybar, st, grad);
   if (const int K = wide_waves(r, cfg, forward_backward_lds_per_wave(T.nloc), false))
     return launch_wide_forward_backward(T, Tb, r, K, y, f, fbar, ebar, ybar, st, grad);
   FusedArgs a{T, Tb.part, Tb.tile_acc, r, y, fbar, ebar, f, ybar};

@@ -8,6 +8,15 @@
 
 namespace cm {
 
+// Tables of the passes that add up by node lists (list_tables in prep.h):
+// stride16 records of 16 bytes per tile; blocks null: the handle has none.
+struct ListTables {
+  const uint4* blocks = nullptr;
+  int32_t stride16 = 0;
+  int32_t chunks = 0;  // most chunks of a tile
+  int32_t groups = 0;  // most groups of 64 nodes of a tile
+};
+
 // Device-resident tables of a prepared batch (see layout.h).
 struct DeviceTables {
   const TileDesc* tiles = nullptr;
@@ -33,6 +42,7 @@ struct DeviceTables {
   const int32_t* cell_tile_first = nullptr;
   const int32_t* cell_tile_count = nullptr;
   int32_t tile_stride = 1;
+  ListTables lists;
   // material slot of every tile (cell * n_regions + region); tiles of slot
   // m: mat_tile_first[m] + k * tile_stride, k < mat_tile_count[m]
   const int32_t* tile_mat = nullptr;
@@ -124,6 +134,23 @@ hipError_t launch_wide_backward(const DeviceTables& T, const Range& r, int K, co
                                 bool grad);
 hipError_t launch_wide_forward_backward(const DeviceTables& T, const DeviceTables& Tb,
                                         const Range& r, int K, const float* y, float* f,
+                                        const float* fbar, const double* ebar, float* ybar,
+                                        hipStream_t st, bool grad);
+
+// Passes with a wavefront per chunk whose contributions are added up by node
+// lists (lists.hip).  list_tiles: largest number of tiles of a handle that
+// gets the tables; use_lists: whether a pass over r takes them.
+int64_t list_tiles();
+bool use_lists(const DeviceTables& T, const Range& r, const LaunchCfg& cfg, bool fwd, bool bwd,
+               bool grad);
+hipError_t launch_list_forward(const DeviceTables& T, const Range& r, const float* y, float* f,
+                               hipStream_t st, const PlateFwd& pl, bool check);
+hipError_t launch_list_backward(const DeviceTables& T, const Range& r, const float* y,
+                                const float* fbar, const double* ebar, float* ybar,
+                                hipStream_t st, const CellMask& mask, const PlateBwd& pl,
+                                bool grad);
+hipError_t launch_list_forward_backward(const DeviceTables& T, const DeviceTables& Tb,
+                                        const Range& r, const float* y, float* f,
                                         const float* fbar, const double* ebar, float* ybar,
                                         hipStream_t st, bool grad);
 

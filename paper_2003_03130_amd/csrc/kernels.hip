@@ -245,6 +245,8 @@ hipError_t launch_forward_main(const DeviceTables& T, const Range& r,
   if (check && !T.tile_nonfin) return hipErrorInvalidValue;
   // the per-wave LDS stride (7 nloc / 4 float4) needs nloc % 4 == 0
   if (T.nloc <= 0 || T.nloc % 4 != 0) return hipErrorInvalidValue;
+  if (use_lists(T, r, cfg, true, false, false))
+    return launch_list_forward(T, r, y, f, st, pl, check);
   if (const int K = wide_waves(r, cfg, forward_lds_per_wave(T.nloc), false))
     return launch_wide_forward(T, r, K, y, f, st, pl, check);
   FwdArgs a{T, r, y, f, pl, check ? 1 : 0};

@@ -893,4 +893,72 @@ int prepare_template(int32_t n_cells, int64_t n_nodes, int64_t n_tets,
   return CM_OK;
 }
 
+bool list_tables(const Prepared& P, ListHost* out) {
+  const int64_t n_tiles = (int64_t)P.tiles.size();
+  // a shared mesh has every tile n_cells times in a row, with one chunk range
+  const int64_t copies = P.tile_stride;
+  int most_chunks = 1, G = 1;
+  for (const TileDesc& d : P.tiles) {
+    most_chunks = std::max(most_chunks, (int)d.n_chunks);
+    G = std::max(G, (d.n_own + d.n_shr + 63) / 64);
+  }
+  if (most_chunks > 255) return false;
+  out->chunks = most_chunks;
+  out->groups = G;
+  out->stride16 = 0;
+  const size_t n_order = (size_t)G * 64, n_lists = ((size_t)G * 2 + 7) & ~(size_t)7;
+  const uint16_t none = (uint16_t)(most_chunks << 8);
+  auto vertex = [](const uint32_t* a, int s) {
+    return (int)((s & 1) ? a[s >> 1] >> 16 : a[s >> 1] & 0xffff);
+  };
+  std::vector<std::vector<uint16_t>> block(n_tiles / copies);
+  std::vector<int32_t> count, order, place, next;
+  for (int64_t t = 0; t < n_tiles; t += copies) {
+    const TileDesc& d = P.tiles[t];
+    const TetChunk* ch = P.chunks.data() + d.chunk_begin;
+    const int nl = d.n_own + d.n_shr;
+    count.assign(nl, 0);
+    for (int k = 0; k < d.n_chunks; ++k)
+      for (int l = 0; l < kChunk; ++l)
+        if (ch[k].a[l][0] != kEmptyLane)
+          for (int s = 0; s < 4; ++s) ++count[vertex(ch[k].a[l], s)];
+    order.resize(nl);
+    std::iota(order.begin(), order.end(), 0);
+    std::stable_sort(order.begin(), order.end(),
+                     [&](int32_t a, int32_t b) { return count[a] > count[b]; });
+    place.resize(nl);
+    for (int i = 0; i < nl; ++i) place[order[i]] = i;
+    std::vector<uint16_t>& o = block[t / copies];
+    o.assign(n_order + n_lists, 0);
+    for (size_t i = 0; i < n_order; ++i) o[i] = i < (size_t)nl ? (uint16_t)order[i] : kNoNode;
+    size_t records = 0;
+    for (int g = 0; g < G; ++g) {
+      // the group's first node has the longest list
+      const int n = 64 * g < nl ? (count[order[64 * g]] + 3) / 4 : 0;
+      if (records + n > 0xffff) return false;
+      o[n_order + 2 * g] = (uint16_t)records;
+      o[n_order + 2 * g + 1] = (uint16_t)n;
+      records += n;
+    }
+    o.resize(n_order + n_lists + records * 256, none);
+    uint16_t* rec = o.data() + n_order + n_lists;
+    next.assign(nl, 0);
+    for (int k = 0; k < d.n_chunks; ++k)
+      for (int s = 0; s < 4; ++s)
+        for (int l = 0; l < kChunk; ++l)
+          if (ch[k].a[l][0] != kEmptyLane) {
+            const int i = place[vertex(ch[k].a[l], s)], j = next[i]++;
+            const size_t first = o[n_order + 2 * (i / 64)];
+            rec[(first + j / 4) * 256 + (size_t)(i % 64) * 4 + j % 4] =
+                (uint16_t)(k << 8 | l << 2 | s);
+          }
+    out->stride16 = std::max(out->stride16, (int32_t)(o.size() / 8));
+  }
+  out->blocks.assign(block.size() * (size_t)out->stride16 * 8, 0);
+  for (size_t b = 0; b < block.size(); ++b)
+    std::copy(block[b].begin(), block[b].end(),
+              out->blocks.begin() + b * (size_t)out->stride16 * 8);
+  return true;
+}
+
 }  // namespace cm

@@ -68,4 +68,25 @@ int prepare_batch(int32_t n_cells, const int64_t* node_off,
                   int32_t n_regions, const PrepOptions& opt, Prepared* out,
                   std::string* err);
 
+// Tables of the passes that add up by node lists (lists.hip): per tile node
+// its contributions (the tetrahedron vertices that name it) in chunk order,
+// within a chunk in vertex slot order.  Per tile (stride16 records of 16
+// bytes):
+//   order    64 `groups` uint16: the tile's nodes, most contributions first
+//            (so that the 64 nodes of a group have lists of nearly one
+//            length), kNoNode after the last;
+//   lists    per group of 64 nodes (first, count) as uint16: `count` records
+//            per node;
+//   records  4 uint16 per node and record, the nodes of a group side by side:
+//            chunk << 8 | lane << 2 | vertex slot, or chunks << 8 (a
+//            contribution of zero) where a node has no more.
+// The copies of a shared mesh share the blocks.  False where the 16-bit
+// numbers do not reach.
+constexpr uint16_t kNoNode = 0xffff;
+struct ListHost {
+  std::vector<uint16_t> blocks;
+  int32_t stride16 = 0, chunks = 0, groups = 0;
+};
+bool list_tables(const Prepared& P, ListHost* out);
+
 }  // namespace cm

@@ -1,12 +1,12 @@
-"""Tile passes with several wavefronts per tile (the default launch) against
-the one-wavefront passes (cm_set_launch with a persistent grid) on the GPU:
-forces, energies, counts, ybar, parameter gradients, Hessian-vector products
-and plate steps must be equal bit for bit -- the wavefronts of a tile add
-their chunks in the order in which one wavefront walks them -- for tiles of
-one chunk (fewer than wavefronts), of 2 to 17 chunks and on both sides of the
-tile counts at which the number of wavefronts changes.  The one-wavefront
-passes are held to the FP64 oracle by the forward, backward and fused tests."""
-
+"""Tile passes with several wavefronts per tile (the default launch: node
+lists up to 256 tiles, turns beyond) against the one-wavefront passes
+(cm_set_launch with a persistent grid) on the GPU: forces, energies, counts,
+ybar, parameter gradients, Hessian-vector products and plate steps must be
+equal bit for bit -- every addition keeps its place -- for tiles of one chunk
+(fewer than wavefronts), of 2 to 17 chunks and more, and on both sides of the
+tile counts at which the pass or its number of wavefronts changes.  The
+one-wavefront passes are held to the FP64 oracle by the forward, backward and
+fused tests."""
 import numpy as np
 import pytest
 
@@ -62,7 +62,7 @@ def _compare(cb, y_host, seed):
     assert torch.equal(got["f2"], got["f"]) and torch.equal(got["ybar2"], got["ybar"])
 
 
-@pytest.mark.parametrize("tile", [64, 128, 192, 320, 768, 1024])
+@pytest.mark.parametrize("tile", [64, 128, 192, 320, 768, 1024, 2048])
 def test_one_cell(tile):
     from paper_2003_03130_amd import CellBatch
     c = small_sphere_case(1003)
@@ -89,9 +89,23 @@ def test_regions():
     _compare(cb, c.y, 1006)
 
 
-# 12 tiles a copy: 1,536 and 1,548 tiles (four wavefronts up to 1,536), 6,492
+@pytest.mark.parametrize("tile", [64, 128, 192, 320, 768, 1024])
+def test_few_chunks_a_tile_in_turns(tile):
+    """As test_one_cell with more than 256 tiles: the turns' tiles of one
+    chunk and more."""
+    from paper_2003_03130_amd import CellBatch
+    c = small_sphere_case(1003)
+    n = CellBatch.single(c.x, c.tets, tile_tets=tile).info["n_tiles"]
+    copies = 256 // n + 1
+    cb = CellBatch.template(copies, c.x, c.tets, tile_tets=tile)
+    assert 256 < cb.info["n_tiles"] <= 1536
+    cb.set_params(*c.theta)
+    _compare(cb, np.tile(c.y, (copies, 1)), 1004)
+
+
+# 12 tiles a copy: 252 and 264 tiles (lists up to 256), 1,536 and 1,548 tiles (four wavefronts up to 1,536), 6,492
 # and 6,504 (four up to 6,500 for the Hessian-vector product)
-@pytest.mark.parametrize("copies", [128, 129, 541, 542])
+@pytest.mark.parametrize("copies", [21, 22, 128, 129, 541, 542])
 def test_tile_counts_where_the_wavefronts_change(copies):
     from paper_2003_03130_amd import CellBatch
     c = small_sphere_case(1000)
