@@ -379,7 +379,9 @@ int cm_autotune(cm_batch h, const float* y, const char* cache_path,
  *   mode 6: forward and backward in one pass (cm_forces_and_backward).
  * Pointers are captured as given and must stay valid while the graph is
  * used.  Re-capturing replaces the previous graph.  cm_graph_launch replays
- * it on `stream` (CM_ESTATE if nothing was captured).
+ * it on `stream` (CM_ESTATE if nothing was captured); modes 0, 1 and 6, two
+ * or four kernels, are replayed as these launches, which costs the host less
+ * than launching a graph.
  */
 int cm_graph_capture(cm_batch h, int mode, const float* y, float* f,
                      double* energy, int32_t* n_inverted, const float* fbar,

@@ -59,8 +59,22 @@ struct cm_batch_s {
   bool params_set = false;
   bool is_template = false;  // cells share one chunk array (tiles interleaved)
   cm::Indenter qs_ind;       // top contact of the quasi-static entry points
+  // captured evaluation (cm_graph_capture): a graph, or the arguments of one
+  // that is two or four launches (mode >= 0)
   hipGraph_t graph = nullptr;
   hipGraphExec_t graph_exec = nullptr;
+  struct Replay {
+    int mode = -1;
+    cm::LaunchCfg cfg;
+    const float* y;
+    float* f;
+    double* energy;
+    int32_t* ninv;
+    const float* fbar;
+    const double* ebar;
+    float* ybar;
+    double* thetabar;
+  } replay;
   // fork/join of the forward and backward branches of a captured graph
   hipStream_t side = nullptr;
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
