@@ -103,16 +103,84 @@ __device__ __forceinline__ void for_each_chunk(const TetChunk* ch, int n,
   for_each_chunk_from(ch, n, lane, ra, body);
 }
 
+// Butterfly over the wavefront with offsets 32, 16, 8, 4, 2, 1: every lane ends
+// with op over all lanes, in the order of that butterfly (op commutative).  The
+// exchanges are register moves -- half-wave and row swaps, then rotations
+// inside a row of 16, which reach lane ^ 8, and lane ^ 4, 2, 1 once the values
+// repeat every 8, 4, 2 lanes -- instead of shuffles through LDS: about 150
+// cycles for a double instead of 700.
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_move(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, true);
+}
+constexpr int kRowRor8 = 0x128, kRowRor4 = 0x124, kQuadXor2 = 0x4e, kQuadXor1 = 0xb1;
+
+template <int CTRL>
+__device__ __forceinline__ int dpp_of(int v) {
+  return (int)dpp_move<CTRL>((uint32_t)v);
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_of(double v) {
+  const uint64_t b = (uint64_t)__double_as_longlong(v);
+  return __longlong_as_double(
+      (long long)((uint64_t)dpp_move<CTRL>((uint32_t)(b >> 32)) << 32 |
+                  dpp_move<CTRL>((uint32_t)b)));
+}
+
+// (a, b) = the values of a lane and of its partner, in one order on both.
+__device__ __forceinline__ void swap32(int v, int& a, int& b) {
+  const auto r = __builtin_amdgcn_permlane32_swap((uint32_t)v, (uint32_t)v, false, false);
+  a = (int)r[0];
+  b = (int)r[1];
+}
+__device__ __forceinline__ void swap16(int v, int& a, int& b) {
+  const auto r = __builtin_amdgcn_permlane16_swap((uint32_t)v, (uint32_t)v, false, false);
+  a = (int)r[0];
+  b = (int)r[1];
+}
+__device__ __forceinline__ double join(int hi, int lo) {
+  return __longlong_as_double((long long)((uint64_t)(uint32_t)hi << 32 | (uint32_t)lo));
+}
+__device__ __forceinline__ void swap32(double v, double& a, double& b) {
+  const uint64_t w = (uint64_t)__double_as_longlong(v);
+  int l0, l1, h0, h1;
+  swap32((int)(uint32_t)w, l0, l1);
+  swap32((int)(uint32_t)(w >> 32), h0, h1);
+  a = join(h0, l0);
+  b = join(h1, l1);
+}
+__device__ __forceinline__ void swap16(double v, double& a, double& b) {
+  const uint64_t w = (uint64_t)__double_as_longlong(v);
+  int l0, l1, h0, h1;
+  swap16((int)(uint32_t)w, l0, l1);
+  swap16((int)(uint32_t)(w >> 32), h0, h1);
+  a = join(h0, l0);
+  b = join(h1, l1);
+}
+
+template <class T, class Op>
+__device__ __forceinline__ T wave_reduce(T v, Op op) {
+  T a, b;
+  swap32(v, a, b);
+  v = op(a, b);
+  swap16(v, a, b);
+  v = op(a, b);
+  v = op(v, dpp_of<kRowRor8>(v));
+  v = op(v, dpp_of<kRowRor4>(v));
+  v = op(v, dpp_of<kQuadXor2>(v));
+  return op(v, dpp_of<kQuadXor1>(v));
+}
+
 __device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-  return v;
+  return wave_reduce(v, [](double a, double b) { return a + b; });
 }
 
 __device__ __forceinline__ int wave_sum(int v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-  return v;
+  return wave_reduce(v, [](int a, int b) { return a + b; });
+}
+
+__device__ __forceinline__ double wave_max(double v) {
+  return wave_reduce(v, [](double a, double b) { return fmax(a, b); });
 }
 
 // Workgroups are dispatched round-robin over the 8 XCDs; give each XCD a

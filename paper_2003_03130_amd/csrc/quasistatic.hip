@@ -32,8 +32,7 @@ constexpr int kResThreads = 512;
 // in wavefront order.  red: at least NT / 64 doubles of LDS.
 template <int NT = kThreads>
 __device__ double block_sum(double v, double* red) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+  v = wave_sum(v);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
   __syncthreads();
   double r = red[0];
@@ -51,10 +50,7 @@ template <int K, int NT = kThreads>
 __device__ void block_sums(double (&v)[K], double* red) {
   constexpr int NW = NT / 64;
 #pragma unroll
-  for (int k = 0; k < K; ++k) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v[k] += __shfl_xor(v[k], off);
-  }
+  for (int k = 0; k < K; ++k) v[k] = wave_sum(v[k]);
   if ((threadIdx.x & 63) == 0) {
 #pragma unroll
     for (int k = 0; k < K; ++k) red[k * NW + (threadIdx.x >> 6)] = v[k];
@@ -73,8 +69,7 @@ __device__ void block_sums(double (&v)[K], double* red) {
 }
 
 __device__ double block_max(double v, double* red) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off));
+  v = wave_max(v);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
   __syncthreads();
   double r = red[0];

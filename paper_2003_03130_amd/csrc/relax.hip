@@ -8,6 +8,7 @@
 #include <hip/hip_runtime.h>
 
 #include "aux_kernels.h"
+#include "device_util.h"
 #include "plate.h"
 
 namespace cm {
@@ -29,8 +30,7 @@ struct StepArgs {
 // Workgroup sum in a fixed order: a butterfly inside each wavefront, then
 // the wavefront totals in wavefront order (deterministic).
 __device__ double block_sum(double v, double* red) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+  v = wave_sum(v);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
   __syncthreads();
   double r = red[0];
