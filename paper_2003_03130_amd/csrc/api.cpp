@@ -134,7 +134,7 @@ static int create_from(cm::Prepared& P, const cm::PrepOptions& po,
   // stream synchronisation below
   std::vector<int32_t> shared_cell, orphan_off, orphan, slot_first, shared_first;
   std::vector<int4> pc, rec, rec4;
-  std::vector<int32_t> more;
+  std::vector<int32_t> more, cand;
   cm::ListHost lists;
   std::vector<int2> nbk;
   {
@@ -248,48 +248,53 @@ static int create_from(cm::Prepared& P, const cm::PrepOptions& po,
       T.lists = cm::ListTables{reinterpret_cast<const uint4*>(blocks), lists.stride16,
                                lists.chunks, lists.groups};
     }
-    // 256 x 256 node-pair blocks of every cell (row block <= column block);
-    // the cell's nodes are ordered candidates first, so the pairs of the
-    // first ceil(candidates / 256) blocks hold every candidate pair
-    // pc: the candidate pair blocks; nbk: the candidate node blocks of every cell
+    // shape diagnostics: the candidates for the largest node distance, and
+    // the block search's tables where a cell has too many of them
+    int most_cand = 0;
+    cand.resize(h->n_cells);
     for (int64_t c = 0; c < h->n_cells; ++c) {
-      const int64_t nb = (P.node_off[c + 1] - P.node_off[c] + 255) / 256;
-      int64_t bc = ((int64_t)P.cell_candidates[c] + 255) / 256;
-      if (bc <= 0) bc = nb;
-      const int base = (int)nbk.size();
-      for (int64_t i = 0; i < bc; ++i) {
-        nbk.push_back(make_int2((int)c, (int)i));
-        for (int64_t j = i; j < bc; ++j)
-          pc.push_back(make_int4((int)c, (int)i, (int)j, base));
+      const int n = (int)(P.node_off[c + 1] - P.node_off[c]);
+      cand[c] = P.cell_candidates[c] > 0 ? P.cell_candidates[c] : n;
+      most_cand = std::max(most_cand, cand[c]);
+    }
+    cm::ShapeTables& S = h->shape;
+    if (most_cand <= cm::kCellNodes) {
+      S.cell_nodes = (most_cand + 63) & ~63;
+    } else {
+      // 256 x 256 node-pair blocks of every cell (row block <= column block);
+      // the cell's nodes are ordered candidates first, so the pairs of the
+      // first ceil(candidates / 256) blocks hold every candidate pair
+      for (int64_t c = 0; c < h->n_cells; ++c) {
+        const int bc = (cand[c] + 255) / 256;
+        const int base = (int)nbk.size();
+        for (int i = 0; i < bc; ++i) {
+          nbk.push_back(make_int2((int)c, i));
+          for (int j = i; j < bc; ++j) pc.push_back(make_int4((int)c, i, j, base));
+        }
       }
     }
     int4* pcd;
     int2* nbd;
-    int32_t *sord, *tinv, *cinv;
+    int32_t *sord, *scand;
     uint64_t* cneg;
-    double *mom, *bbox;
-    unsigned long long* d2;
     if ((rc = h->upload(&pcd, pc, stream)) ||
         (rc = h->upload(&sord, P.space_order, stream)) ||
+        (rc = h->upload(&scand, cand, stream)) ||
         (rc = h->upload(&cneg, P.chunk_neg, stream)) ||
         (rc = h->upload(&nbd, nbk, stream)) ||
-        (rc = h->alloc(&bbox, 6 * nbk.size())) ||
-        (rc = h->alloc(&mom, 10 * (size_t)h->n_tiles)) ||
-        (rc = h->alloc(&tinv, (size_t)h->n_tiles)) ||
-        (rc = h->alloc(&cinv, (size_t)h->n_cells)) ||
-        (rc = h->alloc(&d2, (size_t)h->n_cells)))
+        (rc = h->alloc(&S.bbox, 6 * nbk.size())) ||
+        (rc = h->alloc(&S.mom, 10 * (size_t)h->n_tiles)) ||
+        (rc = h->alloc(&S.tile_inv, (size_t)h->n_tiles)) ||
+        (rc = h->alloc(&S.cell_inv, (size_t)h->n_cells)) ||
+        (rc = h->alloc(&S.d2max, (size_t)h->n_cells)))
       return bail(rc);
-    h->cand_blocks = pcd;
-    h->n_cand_blocks = (int64_t)pc.size();
-    h->shape_tile_inv = tinv;
-    h->chunk_neg = cneg;
-    h->shape_cell_inv = cinv;
-    h->node_blocks = nbd;
-    h->n_node_blocks = (int64_t)nbk.size();
-    h->shape_bbox = bbox;
-    h->space_order = sord;
-    h->shape_mom = mom;
-    h->d2max = d2;
+    S.cand_blocks = pcd;
+    S.n_cand_blocks = (int64_t)pc.size();
+    S.chunk_neg = cneg;
+    S.node_blocks = nbd;
+    S.n_node_blocks = (int64_t)nbk.size();
+    S.order = sord;
+    S.candidates = scand;
     T.params = params;
     T.part = part;
     T.tile_acc = tile_acc;
@@ -1233,10 +1238,7 @@ int cm_shape(cm_batch h, const float* y, const double* d_ref, double* out,
   if (cm::shape_lds(h->T.nloc) > 65536)
     return fail(CM_EINVAL, "tiles too large for the shape kernel's LDS");
   if (int rc = select_device(h)) return rc;
-  CM_HIP(cm::launch_shape(h->T, h->d_node_off, h->cand_blocks, h->n_cand_blocks,
-                          h->node_blocks, h->n_node_blocks, h->space_order, y, d_ref,
-                          h->chunk_neg, h->shape_mom, h->shape_tile_inv, h->shape_cell_inv,
-                          h->shape_bbox, h->d2max, out, stream));
+  CM_HIP(cm::launch_shape(h->T, h->d_node_off, h->shape, y, d_ref, out, stream));
   return CM_OK;
 }
 

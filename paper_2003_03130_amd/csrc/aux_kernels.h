@@ -12,22 +12,37 @@ namespace cm {
 
 // Shape diagnostics (Taylor deformation, cell strain): kShapeFields float64
 // per cell = volume, centre of mass (3), semi-axes a1 <= a2 <= a3, D, d_max,
-// strain.  mom: 10 float64 per tile; d2max: one uint64 per cell; node
-// blocks: (cell, block) for every candidate block of 256 nodes (a cell's
-// nodes ordered candidates first), with a bounding box (6 float64) each;
-// cand_blocks: (cell, row block, column block, first node block of the cell)
-// over the candidate blocks of every cell with row <= column; chunk_neg: per
-// chunk, the lanes of negative reference orientation.
+// strain.
 constexpr int kShapeFields = 10;
+// Most candidates of a cell for the search by one workgroup, which keeps them in
+// LDS (with their boxes 55 KB).
+constexpr int kCellNodes = 4096;
+// Tables and scratch of a handle's shape diagnostics.  cell_nodes: the
+// room of the search of one workgroup per cell, or 0 where some cell has more
+// than kCellNodes candidates; then the block search's tables are there: node
+// blocks (cell, block) of 256 nodes, with a bounding box (6 float64) each, and
+// cand_blocks (cell, row block, column block, first node block of the cell)
+// over the candidate blocks of every cell with row <= column.
+struct ShapeTables {
+  int32_t cell_nodes = 0;
+  const int32_t* order = nullptr;       // per cell, node ids, candidates first,
+                                        // each part in Morton order
+  const int32_t* candidates = nullptr;  // per cell (all its nodes if it has none)
+  const uint64_t* chunk_neg = nullptr;  // per chunk: lanes of negative orientation
+  const int4* cand_blocks = nullptr;
+  int64_t n_cand_blocks = 0;
+  const int2* node_blocks = nullptr;
+  int64_t n_node_blocks = 0;
+  double* mom = nullptr;                // 10 per tile
+  int32_t* tile_inv = nullptr;          // per tile
+  int32_t* cell_inv = nullptr;          // per cell (block search)
+  double* bbox = nullptr;
+  unsigned long long* d2max = nullptr;  // per cell (block search)
+};
 size_t shape_lds(int nloc);
 hipError_t launch_shape(const DeviceTables& T, const int64_t* node_off,
-                        const int4* cand_blocks, int64_t n_cand_blocks,
-                        const int2* node_blocks, int64_t n_node_blocks,
-                        const int32_t* order, const float* y, const double* d_ref,
-                        const uint64_t* chunk_neg, double* mom, int32_t* tile_inv,
-                        int32_t* cell_inv,
-                        double* bbox, unsigned long long* d2max, double* out,
-                        hipStream_t st);
+                        const ShapeTables& S, const float* y, const double* d_ref,
+                        double* out, hipStream_t st);
 
 // Quasi-static plate compression (one workgroup per cell): Newton residual,
 // one conjugate-gradient iteration, bounded Newton update, plate predictor.

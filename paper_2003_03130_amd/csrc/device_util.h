@@ -120,6 +120,10 @@ __device__ __forceinline__ int dpp_of(int v) {
   return (int)dpp_move<CTRL>((uint32_t)v);
 }
 template <int CTRL>
+__device__ __forceinline__ float dpp_of(float v) {
+  return __uint_as_float(dpp_move<CTRL>(__float_as_uint(v)));
+}
+template <int CTRL>
 __device__ __forceinline__ double dpp_of(double v) {
   const uint64_t b = (uint64_t)__double_as_longlong(v);
   return __longlong_as_double(
@@ -137,6 +141,18 @@ __device__ __forceinline__ void swap16(int v, int& a, int& b) {
   const auto r = __builtin_amdgcn_permlane16_swap((uint32_t)v, (uint32_t)v, false, false);
   a = (int)r[0];
   b = (int)r[1];
+}
+__device__ __forceinline__ void swap32(float v, float& a, float& b) {
+  int i, j;
+  swap32(__float_as_int(v), i, j);
+  a = __int_as_float(i);
+  b = __int_as_float(j);
+}
+__device__ __forceinline__ void swap16(float v, float& a, float& b) {
+  int i, j;
+  swap16(__float_as_int(v), i, j);
+  a = __int_as_float(i);
+  b = __int_as_float(j);
 }
 __device__ __forceinline__ double join(int hi, int lo) {
   return __longlong_as_double((long long)((uint64_t)(uint32_t)hi << 32 | (uint32_t)lo));
@@ -158,6 +174,15 @@ __device__ __forceinline__ void swap16(double v, double& a, double& b) {
   b = join(h1, l1);
 }
 
+// The last four offsets: op over each row of 16 lanes.
+template <class T, class Op>
+__device__ __forceinline__ T row_reduce(T v, Op op) {
+  v = op(v, dpp_of<kRowRor8>(v));
+  v = op(v, dpp_of<kRowRor4>(v));
+  v = op(v, dpp_of<kQuadXor2>(v));
+  return op(v, dpp_of<kQuadXor1>(v));
+}
+
 template <class T, class Op>
 __device__ __forceinline__ T wave_reduce(T v, Op op) {
   T a, b;
@@ -165,10 +190,7 @@ __device__ __forceinline__ T wave_reduce(T v, Op op) {
   v = op(a, b);
   swap16(v, a, b);
   v = op(a, b);
-  v = op(v, dpp_of<kRowRor8>(v));
-  v = op(v, dpp_of<kRowRor4>(v));
-  v = op(v, dpp_of<kQuadXor2>(v));
-  return op(v, dpp_of<kQuadXor1>(v));
+  return row_reduce(v, op);
 }
 
 __device__ __forceinline__ double wave_sum(double v) {

@@ -9,6 +9,7 @@
 #include <string>
 #include <vector>
 
+#include "aux_kernels.h"
 #include "cellmech.h"
 #include "kernels.h"
 
@@ -34,18 +35,7 @@ struct cm_batch_s {
   int64_t n_tiles = 0, n_chunks = 0;
   int32_t n_regions = 1;
   int64_t n_mat = 0;  // material slots: n_cells * n_regions
-  // shape diagnostics scratch
-  const int4* cand_blocks = nullptr;  // block pairs among candidate nodes
-  int64_t n_cand_blocks = 0;
-  int32_t* shape_tile_inv = nullptr;
-  const uint64_t* chunk_neg = nullptr;  // per chunk: lanes of negative orientation
-  int32_t* shape_cell_inv = nullptr;
-  const int2* node_blocks = nullptr;
-  int64_t n_node_blocks = 0;
-  const int32_t* space_order = nullptr;
-  double* shape_bbox = nullptr;
-  double* shape_mom = nullptr;
-  unsigned long long* d2max = nullptr;
+  cm::ShapeTables shape;
   int32_t tile_tets = 0, max_tile_nodes = 0;
   double volume = 0, min_v0 = 0, max_cond = 0;
   std::vector<int32_t> cell_tile_off, cell_shared_off;

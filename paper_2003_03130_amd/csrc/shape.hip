@@ -4,18 +4,36 @@
 // taylor-deformation-parameter-definition) and the cell strain (eq.
 // cell-strain).
 //
-//   shape_moments_kernel  one wavefront per tile: the current signed volume
+//   tile_moments          one wavefront per tile: the current signed volume
 //                         V of every tetrahedron and its centroid r, summed
 //                         as V, V r and V r r^T (float64) about a per-cell
 //                         origin (the cell's first node), one record per tile,
 //                         and the tile's count of tetrahedra with V not > 0;
+//   cell_search           one workgroup per cell: the largest distance d_max of
+//                         two nodes;
+//   shape_pass_kernel     both of these, neither of which needs the other;
+//   shape_cell_kernel     one wavefront per cell: the tile records summed in a
+//                         fixed order, the inertia tensor about the centre of
+//                         mass, its eigenvalues by cyclic Jacobi rotations,
+//                         semi-axes, D, and the strain.
+// The farthest two nodes are convex-hull vertices, and a node whose faces are
+// all shared by two tetrahedra on opposite sides lies inside the image of its
+// star while those keep their orientation (their solid angles at the node sum
+// to a positive multiple of 4 pi, so no direction has the node strictly beyond
+// all its neighbours): only the other nodes, the candidates, are searched, and
+// all nodes of a cell with an inverted tetrahedron.
+// Batches with a cell of more than kCellNodes candidates (meshes of some 25,000
+// nodes), which the LDS of a workgroup does not hold, are searched block by block over many
+// workgroups instead (shape_extreme_kernel, shape_bbox_kernel,
+// pair_max_kernel, pair_all_kernel, shape_finalize_kernel, behind
+// shape_moments_kernel):
 //   shape_extreme_kernel  per cell, the nodes extreme along the three axes and
 //                         the four body diagonals; the largest distance among
 //                         these pairs is a lower bound L of d_max (the
 //                         distance of two actual nodes) and starts the maximum;
 //                         and the cell's count of inverted tetrahedra;
 //   shape_bbox_kernel     the bounding box of every candidate block of 256
-//                         nodes (below), the nodes of a cell taken candidates
+//                         nodes, the nodes of a cell taken candidates
 //                         first, each part in Morton order of the reference
 //                         positions;
 //   pair_max_kernel       the largest squared distance between two candidate
@@ -26,19 +44,9 @@
 //                         block pair whose bounding boxes are closer than the
 //                         current maximum cannot hold a larger distance and is
 //                         skipped (the result is the same, only the work
-//                         changes).  The farthest two nodes are convex-hull
-//                         vertices, and a node whose faces are all shared by
-//                         two tetrahedra on opposite sides lies inside the
-//                         image of its star while those keep their orientation
-//                         (their solid angles at the node sum to a positive
-//                         multiple of 4 pi, so no direction has the node
-//                         strictly beyond all its neighbours): the other nodes
-//                         are the candidates;
+//                         changes);
 //   pair_all_kernel       cells with an inverted tetrahedron: all node pairs;
-//   shape_finalize_kernel per cell (one wavefront): tile records summed in a
-//                         fixed order, the inertia tensor about the centre of
-//                         mass, its eigenvalues by cyclic Jacobi rotations,
-//                         semi-axes, D, d_max and the strain.
+//   shape_finalize_kernel per cell (one wavefront) the sums and eigenvalues.
 // Readings: the tensor is taken about the centre of mass; V is the current
 // volume with the reference orientation (negative when inverted); the
 // paper's semi-axis formula gives squared semi-axes of a solid ellipsoid, so
@@ -62,33 +70,42 @@ struct MomArgs {
   double* mom;        // kMom per tile
   int32_t* tile_inv;  // per tile: tetrahedra whose current volume is not > 0
   const uint64_t* chunk_neg;  // per chunk: lanes of negative reference orientation
+  int32_t per_block;          // wavefronts (tiles) of a workgroup that have LDS
 };
 
-__global__ __launch_bounds__(64) void shape_moments_kernel(MomArgs a) {
-  extern __shared__ float4 ys[];
-  const int lane = threadIdx.x;
-  const int t = blockIdx.x;
+// One tile's record, by one wavefront with ys for the tile's nodes.  Of the
+// chunks only the indices are read (8 of every 16 bytes of one row, a third
+// of the chunk), two chunks ahead of their use.
+constexpr int kMomWaves = 8;
+
+__device__ __forceinline__ void tile_moments(const MomArgs& a, int t, int lane, float4* ys) {
   const TileDesc d = a.T.tiles[t];
   const int64_t N = a.T.n_nodes;
+  const TetChunk* ch = a.T.chunks + d.chunk_begin;
+  const uint2 none = make_uint2(kEmptyLane, kEmptyLane);
+  uint2 q0 = none, q1 = none;
+  if (0 < d.n_chunks) q0 = *reinterpret_cast<const uint2*>(ch[0].a[lane]);
+  if (1 < d.n_chunks) q1 = *reinterpret_cast<const uint2*>(ch[1].a[lane]);
   const int64_t o = a.node_off[d.cell];
-  const double ox = a.y[o], oy = a.y[N + o], oz = a.y[2 * N + o];
   for (int l = lane; l < d.n_own + d.n_shr; l += 64) {
     const int64_t g = l < d.n_own ? (int64_t)d.own_begin + l
                                   : (int64_t)a.T.slot_node[d.shr_begin + l - d.n_own];
     ys[l] = make_float4(a.y[g], a.y[N + g], a.y[2 * N + g], 0.f);
   }
+  const double ox = a.y[o], oy = a.y[N + o], oz = a.y[2 * N + o];
   wave_sync();
   double m[kMom];
 #pragma unroll
   for (int j = 0; j < kMom; ++j) m[j] = 0.0;
   int ninv = 0;
-  const TetChunk* ch = a.T.chunks + d.chunk_begin;
   for (int k = 0; k < d.n_chunks; ++k) {
-    const uint2 q = make_uint2(ch[k].a[lane][0], ch[k].a[lane][1]);
     const uint64_t neg = a.chunk_neg[d.chunk_begin + k];  // wave-uniform
-    if (q.x == kEmptyLane) continue;
-    const float4 p[4] = {ys[q.x & 0xffff], ys[q.x >> 16], ys[q.y & 0xffff],
-                         ys[q.y >> 16]};
+    const uint2 c = q0;
+    q0 = q1;
+    if (k + 2 < d.n_chunks) q1 = *reinterpret_cast<const uint2*>(ch[k + 2].a[lane]);
+    if (c.x == kEmptyLane) continue;
+    const float4 p[4] = {ys[c.x & 0xffff], ys[c.x >> 16], ys[c.y & 0xffff],
+                         ys[c.y >> 16]};
     double e[3][3];
 #pragma unroll
     for (int v = 0; v < 3; ++v) {
@@ -124,6 +141,15 @@ __global__ __launch_bounds__(64) void shape_moments_kernel(MomArgs a) {
   }
 }
 
+__global__ __launch_bounds__(64 * kMomWaves) void shape_moments_kernel(MomArgs a) {
+  extern __shared__ float4 ys[];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int64_t t = (int64_t)blockIdx.x * a.per_block + wave;
+  if (wave < a.per_block && t < a.T.n_tiles)
+    tile_moments(a, (int)t, lane, ys + (size_t)wave * a.T.nloc);
+}
+
 struct PairArgs {
   const int4* blocks;  // (cell, row block, column block, first node block of the cell)
   const int64_t* node_off;
@@ -142,6 +168,21 @@ struct AllArgs {
   unsigned long long* d2max;
 };
 
+// Largest squared distance over all node pairs of [n0, n1), this thread's part
+// of a workgroup's 256.
+__device__ __forceinline__ double all_pairs(const float* y, int64_t N, int64_t n0,
+                                            int64_t n1) {
+  double best = 0.0;
+  for (int64_t p = n0 + threadIdx.x; p < n1; p += 256) {
+    const double xp = y[p], yp = y[N + p], zp = y[2 * N + p];
+    for (int64_t q = p + 1; q < n1; ++q) {
+      const double dx = xp - y[q], dy = yp - y[N + q], dz = zp - y[2 * N + q];
+      best = fmax(best, dx * dx + dy * dy + dz * dz);
+    }
+  }
+  return best;
+}
+
 // Cells with an inverted (or degenerate) tetrahedron, which the candidate
 // search does not cover: one workgroup per such cell takes the largest
 // squared distance over all its node pairs (other cells return at once).
@@ -149,17 +190,7 @@ __global__ __launch_bounds__(256) void pair_all_kernel(AllArgs a) {
   __shared__ double red[4];
   const int c = blockIdx.x, tid = threadIdx.x;
   if (a.cell_inv[c] == 0) return;  // uniform over the workgroup
-  const int64_t n0 = a.node_off[c], n1 = a.node_off[c + 1], N = a.N;
-  double best = 0.0;
-  for (int64_t p = n0 + tid; p < n1; p += 256) {
-    const double xp = a.y[p], yp = a.y[N + p], zp = a.y[2 * N + p];
-    for (int64_t q = p + 1; q < n1; ++q) {
-      const double dx = xp - a.y[q], dy = yp - a.y[N + q], dz = zp - a.y[2 * N + q];
-      best = fmax(best, dx * dx + dy * dy + dz * dz);
-    }
-  }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) best = fmax(best, __shfl_xor(best, off));
+  const double best = wave_max(all_pairs(a.y, a.N, a.node_off[c], a.node_off[c + 1]));
   if ((tid & 63) == 0) red[tid >> 6] = best;
   __syncthreads();
   if (tid == 0) {
@@ -397,12 +428,10 @@ struct ShapeFinArgs {
   double* out;          // kShapeFields per cell
 };
 
-// One wavefront per cell: lane l sums the tile records l, l + 64, ...,
-// then a fixed butterfly; lane 0 finishes the cell.
-__global__ __launch_bounds__(256) void shape_finalize_kernel(ShapeFinArgs a) {
-  const int c = (int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
-  const int lane = threadIdx.x & 63;
-  if (c >= a.T.n_cells) return;  // uniform per wavefront
+// The fields of cell c but d_max and the strain, on one wavefront: lane l sums
+// the tile records l, l + 64, ..., then a fixed butterfly; lane 0 finishes the
+// cell.
+__device__ void shape_fields(const ShapeFinArgs& a, int c, int lane) {
   double m[kMom];
 #pragma unroll
   for (int j = 0; j < kMom; ++j) m[j] = 0.0;
@@ -433,7 +462,6 @@ __global__ __launch_bounds__(256) void shape_finalize_kernel(ShapeFinArgs a) {
   const double a1 = sqrt(fmax(f * (-th[0] + th[1] + th[2]), 0.0));
   const double a2 = sqrt(fmax(f * (th[0] - th[1] + th[2]), 0.0));
   const double a3 = sqrt(fmax(f * (th[0] + th[1] - th[2]), 0.0));
-  const double dmax = sqrt(__longlong_as_double((long long)a.d2max[c]));
   double* r = a.out + (int64_t)kShapeFields * c;
   r[0] = M;
   r[1] = (double)a.y[o] + cx;
@@ -441,49 +469,340 @@ __global__ __launch_bounds__(256) void shape_finalize_kernel(ShapeFinArgs a) {
   r[3] = (double)a.y[2 * N + o] + cz;
   r[4] = a1; r[5] = a2; r[6] = a3;
   r[7] = (a3 - a1) / (a3 + a1);
+}
+
+__device__ __forceinline__ void shape_distance(const ShapeFinArgs& a, int c, double d2) {
+  const double dmax = sqrt(d2);
+  double* r = a.out + (int64_t)kShapeFields * c;
   r[8] = dmax;
   r[9] = a.d_ref ? (dmax - a.d_ref[c]) / a.d_ref[c] : __builtin_nan("");
+}
+
+__global__ __launch_bounds__(256) void shape_finalize_kernel(ShapeFinArgs a) {
+  const int c = (int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
+  const int lane = threadIdx.x & 63;
+  if (c >= a.T.n_cells) return;  // uniform per wavefront
+  shape_fields(a, c, lane);
+  if (lane == 0) shape_distance(a, c, __longlong_as_double((long long)a.d2max[c]));
+}
+
+// ------------------------------------------------- one workgroup per cell
+__device__ __forceinline__ double dist2(double dx, double dy, double dz) {
+  return dx * dx + dy * dy + dz * dz;
+}
+
+constexpr int kCellThreads = 64 * kMomWaves;
+constexpr int kGroup = 16;  // nodes that share a bounding box
+
+struct CellArgs {
+  MomArgs mom;
+  const int32_t* order;       // per cell, node ids, candidates first
+  const int32_t* candidates;  // per cell: how many of them are candidates
+  unsigned long long* d2max;
+  int32_t cap;                // nodes that the LDS holds (multiple of 64)
+};
+
+// Largest value over the workgroup (v >= 0) on every thread, and one of the
+// places it was found at.
+__device__ __forceinline__ void cell_argmax(double& v, int& i, double* rv, int* ri) {
+  const double m = wave_max(v);
+  const int first = __ffsll((long long)__ballot(v == m)) - 1;
+  i = __shfl(i, first);
+  if ((threadIdx.x & 63) == 0) { rv[threadIdx.x >> 6] = m; ri[threadIdx.x >> 6] = i; }
+  __syncthreads();
+  v = rv[0];
+  i = ri[0];
+#pragma unroll
+  for (int w = 1; w < kMomWaves; ++w)
+    if (rv[w] > v) { v = rv[w]; i = ri[w]; }
+  __syncthreads();  // rv, ri are used again
+}
+
+struct Min { __device__ float operator()(float a, float b) const { return fminf(a, b); } };
+struct Max { __device__ float operator()(float a, float b) const { return fmaxf(a, b); } };
+
+// The largest squared distance of two candidates of cell c, by one workgroup.
+// The candidates' positions are kept in LDS.  From the node farthest from the
+// centre of their box (at distance R), three steps to the node farthest from
+// the last one give a pair whose distance L is a lower bound of d_max, mostly
+// d_max itself.  A node nearer to the centre than L - R has no partner at L or
+// more: the others, in order, are what remains (a few at the tips of an
+// elongated cell, a ring of a flat one, all of a sphere).  They are compact in
+// groups of 16 (Morton order), each with its bounding box: a wavefront takes 64
+// of them, one per lane, and goes over a group only if the boxes, and then some
+// lane's node and the box, could be farther apart than the largest distance so
+// far.  All tests keep a relative margin of 1e-12 against the rounding of the
+// sums, so the result is that of all pairs.
+__device__ __forceinline__ void cell_search(const CellArgs& a, int c, float* sx) {
+  __shared__ double rv[kMomWaves];
+  __shared__ int ri[kMomWaves];
+  __shared__ float rb[kMomWaves][6];
+  __shared__ unsigned long long best_bits;
+  const float* y = a.mom.y;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t n0 = a.mom.node_off[c], N = a.mom.T.n_nodes;
+  const int ns = a.candidates[c];
+  float *sy = sx + a.cap, *sz = sy + a.cap, *box = sz + a.cap;
+  float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
+  for (int b = 0; b < ns; b += 4 * kCellThreads) {  // four gathers in flight
+    int64_t g[4];
+    float p[4][3];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      g[u] = a.order[n0 + min(b + u * kCellThreads + tid, ns - 1)];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      p[u][0] = y[g[u]];
+      p[u][1] = y[N + g[u]];
+      p[u][2] = y[2 * N + g[u]];
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        lo[d] = fminf(lo[d], p[u][d]);
+        hi[d] = fmaxf(hi[d], p[u][d]);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int i = b + u * kCellThreads + tid;
+      if (i < ns) { sx[i] = p[u][0]; sy[i] = p[u][1]; sz[i] = p[u][2]; }
+    }
+  }
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    const float l = wave_reduce(lo[d], Min()), h = wave_reduce(hi[d], Max());
+    if (lane == 0) { rb[wave][d] = l; rb[wave][3 + d] = h; }
+  }
+  __syncthreads();
+  double ctr[3];
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    float l = rb[0][d], h = rb[0][3 + d];
+#pragma unroll
+    for (int w = 1; w < kMomWaves; ++w) {
+      l = fminf(l, rb[w][d]);
+      h = fmaxf(h, rb[w][3 + d]);
+    }
+    ctr[d] = 0.5 * ((double)l + (double)h);
+  }
+  // farthest from the centre, then from the node found last
+  const double cx = ctr[0], cy = ctr[1], cz = ctr[2];
+  double px = cx, py = cy, pz = cz, R2 = 0.0, L2 = 0.0;
+  for (int step = 0; step < 4; ++step) {
+    double v = 0.0;
+    int i = 0;
+    for (int k = tid; k < ns; k += kCellThreads) {
+      const double d2 = dist2(px - sx[k], py - sy[k], pz - sz[k]);
+      if (d2 > v) { v = d2; i = k; }
+    }
+    cell_argmax(v, i, rv, ri);
+    if (step == 0) {
+      R2 = v;
+    } else {
+      if (!(v > L2)) break;  // uniform: the last pair is mutually farthest
+      L2 = v;
+    }
+    px = sx[i]; py = sy[i]; pz = sz[i];
+  }
+  // the nodes that remain, in place and in order (all of them if L - R is not
+  // positive, or no number)
+  const double gap = sqrt(L2) * (1.0 - 1e-12) - sqrt(R2) * (1.0 + 1e-12);
+  const double least2 = gap > 0.0 ? gap * gap * (1.0 - 1e-12) : 0.0;
+  int kept = 0;
+  for (int b = 0; b < ns; b += kCellThreads) {
+    const int k = b + tid;
+    float x = 0.f, yk = 0.f, z = 0.f;
+    bool keep = false;
+    if (k < ns) {
+      x = sx[k]; yk = sy[k]; z = sz[k];
+      keep = !(dist2(x - cx, yk - cy, z - cz) < least2);
+    }
+    const unsigned long long m = __ballot(keep);
+    if (lane == 0) ri[wave] = __popcll(m);
+    __syncthreads();  // (all positions of this round are in registers)
+    int at = kept;
+#pragma unroll
+    for (int w = 0; w < kMomWaves; ++w) {
+      if (w < wave) at += ri[w];
+      kept += ri[w];
+    }
+    if (keep) {
+      at += __popcll(m & ((1ull << lane) - 1));
+      sx[at] = x; sy[at] = yk; sz[at] = z;
+    }
+    __syncthreads();  // ri is used again
+  }
+  // the last 64 are filled up with the last node, then the boxes
+  const int blocks = (kept + 63) / 64;
+  for (int b = wave; b < blocks; b += kMomWaves) {
+    const int k = 64 * b + lane, from = min(k, kept - 1);
+    const float v[3] = {sx[from], sy[from], sz[from]};
+    wave_sync();
+    if (k >= kept) { sx[k] = v[0]; sy[k] = v[1]; sz[k] = v[2]; }
+    float* to = box + 6 * (k / kGroup);
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      const float lo = row_reduce(v[d], Min()), hi = row_reduce(v[d], Max());
+      if ((lane & 15) == 0) { to[d] = lo; to[3 + d] = hi; }
+    }
+  }
+  if (tid == 0) best_bits = (unsigned long long)__double_as_longlong(L2);
+  __syncthreads();
+  // 64 rows (one a lane) against 64 column groups (one a lane for the test of
+  // boxes) at a time, round the wavefronts
+  double best = L2;  // per lane
+  const int groups = blocks * (64 / kGroup);
+  int turn = 0;
+  for (int g = 0; g < blocks; ++g)
+    for (int h0 = g * (64 / kGroup); h0 < groups; h0 += 64) {
+      const bool mine = turn == wave;
+      turn = turn + 1 == kMomWaves ? 0 : turn + 1;
+      if (!mine) continue;
+      const double best0 = __longlong_as_double((long long)__hip_atomic_load(
+          &best_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+      best = fmax(best, best0);
+      bool near = false;
+      if (h0 + lane < groups) {
+        const float* q = box + 6 * (h0 + lane);
+        const double q0 = q[0], q1 = q[1], q2 = q[2], q3 = q[3], q4 = q[4], q5 = q[5];
+#pragma unroll
+        for (int s = 0; s < 64 / kGroup; ++s) {
+          const float* r = box + 6 * (g * (64 / kGroup) + s);
+          const double ex = fmax(r[3] - q0, q3 - r[0]), ey = fmax(r[4] - q1, q4 - r[1]),
+                       ez = fmax(r[5] - q2, q5 - r[2]);
+          near |= !(dist2(ex, ey, ez) < best0 * (1.0 - 1e-12));
+        }
+      }
+      const double x = sx[64 * g + lane], yk = sy[64 * g + lane], z = sz[64 * g + lane];
+      for (unsigned long long todo = __ballot(near); todo != 0; todo &= todo - 1) {
+        const int h = h0 + __ffsll((long long)todo) - 1;
+        const float* q = box + 6 * h;
+        const double ex = fmax(x - q[0], q[3] - x), ey = fmax(yk - q[1], q[4] - yk),
+                     ez = fmax(z - q[2], q[5] - z);
+        if (__ballot(!(dist2(ex, ey, ez) < best * (1.0 - 1e-12))) == 0) continue;
+        const float4* vx = reinterpret_cast<const float4*>(sx + kGroup * h);
+        const float4* vy = reinterpret_cast<const float4*>(sy + kGroup * h);
+        const float4* vz = reinterpret_cast<const float4*>(sz + kGroup * h);
+#pragma unroll
+        for (int j = 0; j < kGroup / 4; ++j) {
+          const float4 u = vx[j], v = vy[j], w = vz[j];
+          best = fmax(best, dist2(x - u.x, yk - v.x, z - w.x));
+          best = fmax(best, dist2(x - u.y, yk - v.y, z - w.y));
+          best = fmax(best, dist2(x - u.z, yk - v.z, z - w.z));
+          best = fmax(best, dist2(x - u.w, yk - v.w, z - w.w));
+        }
+      }
+      // the maximum of non-negative doubles is that of their bit patterns
+      if (__ballot(best > best0) != 0) {
+        best = wave_max(best);
+        if (lane == 0)
+          atomicMax(&best_bits, (unsigned long long)__double_as_longlong(best));
+      }
+    }
+  __syncthreads();
+  if (tid == 0) a.d2max[c] = best_bits;
+}
+
+// The searches, one workgroup per cell, and behind them in the same launch the
+// tile records, a wavefront per tile.  Both are bound by their chains of
+// dependent loads, which overlap here; six launches in a row before (records,
+// extreme nodes, boxes, pairs of blocks of 256, all pairs of inverted cells,
+// fields).  512 cells of 1,000 to 9,000 nodes, 5 M tets: 131 -> 42 us for
+// cm_shape, of which 33 here and 9 in shape_cell_kernel (its eigenvalues are a
+// chain of divisions and square roots); 64 cells of 20,000 nodes 200 -> 42, one
+// of 1,000 nodes 43 -> 14; 1,024 equal spheres of 2,000 nodes, where every
+// candidate remains, 189 -> 141.
+__global__ __launch_bounds__(kCellThreads) void shape_pass_kernel(CellArgs a) {
+  extern __shared__ float4 lds[];
+  const int nc = a.mom.T.n_cells;
+  if ((int)blockIdx.x < nc) {
+    cell_search(a, blockIdx.x, reinterpret_cast<float*>(lds));
+    return;
+  }
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int64_t t = (int64_t)((int)blockIdx.x - nc) * a.mom.per_block + wave;
+  if (wave < a.mom.per_block && t < a.mom.T.n_tiles)
+    tile_moments(a.mom, (int)t, lane, lds + (size_t)wave * a.mom.T.nloc);
+}
+
+// The cell's fields, by one wavefront; all four search all node pairs first if
+// the cell has a tetrahedron that is not positively oriented, which the
+// candidates do not cover.
+__global__ __launch_bounds__(256) void shape_cell_kernel(ShapeFinArgs f,
+                                                         const int32_t* tile_inv) {
+  __shared__ double rv[4];
+  const int c = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+  int inv = 0;
+  {
+    const int t0 = f.T.cell_tile_first[c], nt = f.T.cell_tile_count[c];
+    for (int k = tid; k < nt; k += 256)
+      inv |= tile_inv[t0 + (int64_t)k * f.T.tile_stride];
+  }
+  double d2 = __longlong_as_double((long long)f.d2max[c]);
+  if (__syncthreads_or(inv != 0)) {
+    const double m = wave_max(all_pairs(f.y, f.T.n_nodes, f.node_off[c], f.node_off[c + 1]));
+    if (lane == 0) rv[tid >> 6] = m;
+    __syncthreads();
+    d2 = fmax(fmax(d2, fmax(rv[0], rv[1])), fmax(rv[2], rv[3]));
+  }
+  if (tid >= 64) return;
+  shape_fields(f, c, lane);
+  if (lane == 0) shape_distance(f, c, d2);
 }
 
 }  // namespace
 
 size_t shape_lds(int nloc) { return (size_t)16 * nloc; }
 
+// LDS of the search of one workgroup per cell, for cap nodes: positions, boxes.
+static size_t cell_lds(int cap) { return (size_t)12 * cap + (size_t)24 * (cap / kGroup); }
+
 hipError_t launch_shape(const DeviceTables& T, const int64_t* node_off,
-                        const int4* cand_blocks, int64_t n_cand_blocks,
-                        const int2* node_blocks, int64_t n_node_blocks,
-                        const int32_t* order, const float* y, const double* d_ref,
-                        const uint64_t* chunk_neg, double* mom, int32_t* tile_inv,
-                        int32_t* cell_inv,
-                        double* bbox, unsigned long long* d2max, double* out,
-                        hipStream_t st) {
+                        const ShapeTables& S, const float* y, const double* d_ref,
+                        double* out, hipStream_t st) {
   const int nc = T.n_cells;
   hipError_t e;
-  if (T.n_tiles > 0) {
-    MomArgs m{T, node_off, y, mom, tile_inv, chunk_neg};
-    hipLaunchKernelGGL(shape_moments_kernel, dim3((unsigned)T.n_tiles), dim3(64),
-                       shape_lds(T.nloc), st, m);
+  // (the caller checks that one tile fits 64 KB; of large tiles a workgroup
+  // takes one)
+  const int per =
+      std::min(kMomWaves, std::max(1, (int)(65536 / std::max<size_t>(shape_lds(T.nloc), 1))));
+  const MomArgs m{T, node_off, y, S.mom, S.tile_inv, S.chunk_neg, per};
+  const unsigned mom_blocks = (unsigned)((T.n_tiles + per - 1) / per);
+  const size_t mom_lds = per * shape_lds(T.nloc);
+  const ShapeFinArgs f{T, node_off, y, S.mom, S.d2max, d_ref, out};
+  if (S.cell_nodes > 0) {
+    const CellArgs a{m, S.order, S.candidates, S.d2max, S.cell_nodes};
+    hipLaunchKernelGGL(shape_pass_kernel, dim3(nc + mom_blocks), dim3(kCellThreads),
+                       std::max(mom_lds, cell_lds(S.cell_nodes)), st, a);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    hipLaunchKernelGGL(shape_cell_kernel, dim3(nc), dim3(256), 0, st, f,
+                       (const int32_t*)S.tile_inv);
+    return hipGetLastError();
+  }
+  if (mom_blocks > 0) {
+    hipLaunchKernelGGL(shape_moments_kernel, dim3(mom_blocks), dim3(64 * kMomWaves),
+                       mom_lds, st, m);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  ExtArgs x{T, node_off, y, T.n_nodes, d2max, tile_inv, cell_inv};
+  ExtArgs x{T, node_off, y, T.n_nodes, S.d2max, S.tile_inv, S.cell_inv};
   hipLaunchKernelGGL(shape_extreme_kernel, dim3(nc), dim3(256), 0, st, x);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  if (n_node_blocks > 0) {
-    BoxArgs bx{node_blocks, node_off, order, y, T.n_nodes, bbox};
-    hipLaunchKernelGGL(shape_bbox_kernel, dim3((unsigned)n_node_blocks), dim3(256), 0,
+  if (S.n_node_blocks > 0) {
+    BoxArgs bx{S.node_blocks, node_off, S.order, y, T.n_nodes, S.bbox};
+    hipLaunchKernelGGL(shape_bbox_kernel, dim3((unsigned)S.n_node_blocks), dim3(256), 0,
                        st, bx);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  if (n_cand_blocks > 0) {
-    PairArgs p{cand_blocks, node_off, order, y, T.n_nodes, bbox, d2max};
-    hipLaunchKernelGGL(pair_max_kernel, dim3((unsigned)n_cand_blocks), dim3(256), 0,
+  if (S.n_cand_blocks > 0) {
+    PairArgs p{S.cand_blocks, node_off, S.order, y, T.n_nodes, S.bbox, S.d2max};
+    hipLaunchKernelGGL(pair_max_kernel, dim3((unsigned)S.n_cand_blocks), dim3(256), 0,
                        st, p);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  AllArgs al{node_off, y, T.n_nodes, cell_inv, d2max};
+  AllArgs al{node_off, y, T.n_nodes, S.cell_inv, S.d2max};
   hipLaunchKernelGGL(pair_all_kernel, dim3(nc), dim3(256), 0, st, al);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  ShapeFinArgs f{T, node_off, y, mom, d2max, d_ref, out};
   hipLaunchKernelGGL(shape_finalize_kernel, dim3((nc + 3) / 4), dim3(256), 0, st, f);
   return hipGetLastError();
 }
