@@ -135,6 +135,7 @@ static int create_from(cm::Prepared& P, const cm::PrepOptions& po,
   std::vector<int32_t> shared_cell, orphan_off, orphan, slot_first, shared_first;
   std::vector<int4> pc, rec, rec4;
   std::vector<int32_t> more, cand;
+  std::vector<uint32_t> done;
   cm::ListHost lists;
   std::vector<int2> nbk;
   {
@@ -306,6 +307,21 @@ static int create_from(cm::Prepared& P, const cm::PrepOptions& po,
     h->Tb.tile_acc = tile_acc_b;
     h->Tb.tile_ninv = nullptr;
     h->Tb.tile_nonfin = nullptr;
+    // arrival counters of the passes that form the cells' sums themselves, one
+    // set for either direction (they may run beside each other)
+    bool tiles_everywhere = true;
+    for (int64_t c = 0; c < h->n_cells; ++c) {
+      tiles_everywhere = tiles_everywhere && P.cell_tile_count[c] > 0;
+      T.max_cell_shared = std::max(T.max_cell_shared,
+                                   P.cell_shared_off[c + 1] - P.cell_shared_off[c]);
+    }
+    h->Tb.max_cell_shared = T.max_cell_shared;
+    if (tiles_everywhere && h->n_tiles <= cm::list_tiles()) {
+      const int64_t n = h->n_cells * cm::kDoneStride;
+      done.assign(2 * n, 0);
+      if ((rc = h->upload(&T.cell_done, done, stream))) return bail(rc);
+      h->Tb.cell_done = T.cell_done + n;
+    }
   }
   for (cm::DeviceTables* t : {&h->T, &h->Tb}) {
     t->n_nodes = h->n_nodes;

@@ -245,13 +245,13 @@ hipError_t launch_backward_main(const DeviceTables& T, const Range& r,
                                 const LaunchCfg& cfg, const float* y,
                                 const float* fbar, const double* ebar,
                                 float* ybar, hipStream_t st, const CellMask& mask,
-                                const PlateBwd& pl, bool grad) {
+                                const PlateBwd& pl, bool grad, const CellOut& out) {
   if (r.tile_end <= r.tile_begin) return hipSuccess;
   // the per-wave LDS stride (10 nloc / 4 float4) needs nloc % 4 == 0, else
   // a wave's last float2 would overlap the next wave's records
   if (T.nloc <= 0 || T.nloc % 4 != 0) return hipErrorInvalidValue;
   if (use_lists(T, r, cfg, false, true, grad))
-    return launch_list_backward(T, r, y, fbar, ebar, ybar, st, mask, pl, grad);
+    return launch_list_backward(T, r, y, fbar, ebar, ybar, st, mask, pl, grad, out);
   if (const int K = wide_waves(r, cfg, backward_lds_per_wave(T.nloc), !grad))
     return launch_wide_backward(T, r, K, y, fbar, ebar, ybar, st, mask, pl, grad);
   BwdArgs a{T, r, y, fbar, ebar, ybar, mask, pl};
@@ -292,8 +292,10 @@ hipError_t launch_backward(const DeviceTables& T, const Range& r,
   // without them the pass is the Hessian-vector product alone
   const bool grad = ebar != nullptr || (pl.plate ? pl.thetabar_acc != nullptr
                                                  : thetabar != nullptr);
-  hipError_t e = launch_backward_main(T, r, cfg, y, fbar, ebar, ybar, st, mask, pl, grad);
-  if (e != hipSuccess) return e;
+  const bool tail = use_tail(T, r, cfg, false, true, grad);
+  const CellOut out{tail ? T.cell_done : nullptr, nullptr, nullptr, nullptr, thetabar};
+  hipError_t e = launch_backward_main(T, r, cfg, y, fbar, ebar, ybar, st, mask, pl, grad, out);
+  if (e != hipSuccess || tail) return e;
   return launch_backward_finalize(T, r, ybar, thetabar, st, mask, y, fbar, pl);
 }
 

@@ -16,6 +16,48 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_wave_barrier();
 }
 
+// Stores and loads past the caches that other XCDs do not see: relaxed atomics
+// of device scope (such a store has arrived once the wavefront has waited for
+// it).
+template <class T>
+__device__ __forceinline__ void device_store(T* p, T v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <class T>
+__device__ __forceinline__ T device_load(const T* p) {
+  return __hip_atomic_load(const_cast<T*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Three floats at base + 3 i (bytes below 4 GiB) in one access.
+typedef uint32_t u32x3_t __attribute__((ext_vector_type(3)));
+constexpr int kDeviceScope = 16;  // the instructions' sc1 bit
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t device_rsrc(const float* base) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), 0, -1, 0x00027000);
+}
+__device__ __forceinline__ void device_load3(const float* base, int32_t i, float (&v)[3]) {
+  const u32x3_t r = __builtin_amdgcn_raw_buffer_load_b96(device_rsrc(base), 12 * i, 0,
+                                                         kDeviceScope);
+  v[0] = __uint_as_float(r.x);
+  v[1] = __uint_as_float(r.y);
+  v[2] = __uint_as_float(r.z);
+}
+__device__ __forceinline__ void device_store3(float* base, int32_t i, const float v[3]) {
+  const u32x3_t r = {__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2])};
+  __builtin_amdgcn_raw_buffer_store_b96(r, device_rsrc(base), 12 * i, 0, kDeviceScope);
+}
+template <bool DEVICE, class T>
+__device__ __forceinline__ void store_as(T* p, T v) {
+  if constexpr (DEVICE)
+    device_store(p, v);
+  else
+    *p = v;
+}
+template <bool DEVICE, class T>
+__device__ __forceinline__ T load_as(const T* p) {
+  if constexpr (DEVICE) return device_load(p);
+  return *p;
+}
+
 // One lane's tetrahedron of a chunk: packed local indices, B and V0.
 struct TetRegs {
   uint2 q;

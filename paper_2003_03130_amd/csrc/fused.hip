@@ -237,14 +237,14 @@ hipError_t launch_forward_backward_main(const DeviceTables& T, const DeviceTable
                                         const Range& r, const LaunchCfg& cfg,
                                         const float* y, float* f, const float* fbar,
                                         const double* ebar, float* ybar, hipStream_t st,
-                                        bool grad) {
+                                        bool grad, const CellOut& out) {
   if (r.tile_end <= r.tile_begin) return hipSuccess;
   // every layout rounds nloc up to a multiple of 4 (the separate passes'
   // LDS strides need it; this pass's 48-byte stride keeps its float4
   // records aligned for any nloc)
   if (T.nloc <= 0 || T.nloc % 4 != 0) return hipErrorInvalidValue;
   if (use_lists(T, r, cfg, true, true, grad))
-    return launch_list_forward_backward(T, Tb, r, y, f, fbar, ebar, ybar, st, grad);
+    return launch_list_forward_backward(T, Tb, r, y, f, fbar, ebar, ybar, st, grad, out);
   if (const int K = wide_waves(r, cfg, forward_backward_lds_per_wave(T.nloc), false))
     return launch_wide_forward_backward(T, Tb, r, K, y, f, fbar, ebar, ybar, st, grad);
   FusedArgs a{T, Tb.part, Tb.tile_acc, r, y, fbar, ebar, f, ybar};
@@ -267,9 +267,11 @@ hipError_t launch_forward_backward(const DeviceTables& T, const DeviceTables& Tb
   // as in the backward pass: without an energy cotangent or a parameter
   // gradient the adjoint half is the Hessian-vector product alone
   const bool grad = ebar != nullptr || thetabar != nullptr;
+  const bool tail = use_tail(T, r, cfg, true, true, grad);
+  const CellOut out{tail ? T.cell_done : nullptr, energy, ninv, nullptr, thetabar};
   hipError_t e =
-      launch_forward_backward_main(T, Tb, r, cfg, y, f, fbar, ebar, ybar, st, grad);
-  if (e != hipSuccess) return e;
+      launch_forward_backward_main(T, Tb, r, cfg, y, f, fbar, ebar, ybar, st, grad, out);
+  if (e != hipSuccess || tail) return e;
   return launch_forward_backward_finalize(T, Tb, r, f, energy, ninv, ybar, thetabar, st);
 }
 

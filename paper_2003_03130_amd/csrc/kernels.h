@@ -17,6 +17,9 @@ struct ListTables {
   int32_t groups = 0;  // most groups of 64 nodes of a tile
 };
 
+// One counter per cache line (its atomics are served one after the other).
+constexpr int kDoneStride = 32;
+
 // Device-resident tables of a prepared batch (see layout.h).
 struct DeviceTables {
   const TileDesc* tiles = nullptr;
@@ -57,6 +60,10 @@ struct DeviceTables {
   int32_t* tile_ninv = nullptr;    // per tile
   int32_t* tile_nonfin = nullptr;  // per tile: tets with a non-finite energy
                                    // or force (written by checked passes)
+  // per cell, kDoneStride apart: tiles that have arrived in a pass that forms
+  // the cell's sums itself (tail.h); null where some cell has no tile
+  uint32_t* cell_done = nullptr;
+  int32_t max_cell_shared = 0;     // most shared nodes of a cell
   int64_t n_nodes = 0, n_slots = 0, n_tiles = 0;
   int32_t n_cells = 0;
   int32_t nloc = 0;                // LDS node capacity per wave (multiple of 4)
@@ -116,6 +123,16 @@ struct LaunchCfg {
   int blocks = 0;  // persistent workgroups; 0 = one workgroup per W tiles
 };
 
+// Per-cell outputs of a tile pass that forms the cells' sums itself (done set:
+// DeviceTables::cell_done), without a finalize launch behind it.
+struct CellOut {
+  uint32_t* done = nullptr;
+  double* energy = nullptr;    // nullable, as all of these
+  int32_t* ninv = nullptr;
+  int32_t* nonfin = nullptr;
+  double* thetabar = nullptr;
+};
+
 // LDS bytes per wave of the forward / backward kernel for nloc tile nodes.
 size_t forward_lds_per_wave(int nloc);
 size_t backward_lds_per_wave(int nloc);
@@ -144,17 +161,23 @@ int64_t list_tiles();
 bool use_lists(const DeviceTables& T, const Range& r, const LaunchCfg& cfg, bool fwd, bool bwd,
                bool grad);
 hipError_t launch_list_forward(const DeviceTables& T, const Range& r, const float* y, float* f,
-                               hipStream_t st, const PlateFwd& pl, bool check);
+                               hipStream_t st, const PlateFwd& pl, bool check,
+                               const CellOut& out);
 hipError_t launch_list_backward(const DeviceTables& T, const Range& r, const float* y,
                                 const float* fbar, const double* ebar, float* ybar,
                                 hipStream_t st, const CellMask& mask, const PlateBwd& pl,
-                                bool grad);
+                                bool grad, const CellOut& out);
 hipError_t launch_list_forward_backward(const DeviceTables& T, const DeviceTables& Tb,
                                         const Range& r, const float* y, float* f,
                                         const float* fbar, const double* ebar, float* ybar,
-                                        hipStream_t st, bool grad);
+                                        hipStream_t st, bool grad, const CellOut& out);
 
-// The two kernels of each pass, separately (for per-kernel timing).
+// Whether a pass over r forms the cells' sums itself.
+bool use_tail(const DeviceTables& T, const Range& r, const LaunchCfg& cfg, bool fwd, bool bwd,
+              bool grad);
+
+// The two kernels of each pass, separately (for per-kernel timing); with out.done
+// set (use_tail), the first forms the cells' sums too.
 // With pl.plate set, the forward pass applies one plate-compression step
 // (see plate.h): it writes pl.y_next (and pl.force) instead of f, and the
 // finalize kernel needs y.
@@ -164,7 +187,7 @@ hipError_t launch_list_forward_backward(const DeviceTables& T, const DeviceTable
 hipError_t launch_forward_main(const DeviceTables& T, const Range& r,
                                const LaunchCfg& cfg, const float* y, float* f,
                                hipStream_t st, const PlateFwd& pl = PlateFwd{},
-                               bool check = false);
+                               bool check = false, const CellOut& out = CellOut{});
 hipError_t launch_forward_finalize(const DeviceTables& T, const Range& r,
                                    float* f, double* energy, int32_t* ninv,
                                    hipStream_t st, const float* y = nullptr,
@@ -177,7 +200,8 @@ hipError_t launch_backward_main(const DeviceTables& T, const Range& r,
                                 const float* fbar, const double* ebar,
                                 float* ybar, hipStream_t st,
                                 const CellMask& mask = CellMask{},
-                                const PlateBwd& pl = PlateBwd{}, bool grad = true);
+                                const PlateBwd& pl = PlateBwd{}, bool grad = true,
+                                const CellOut& out = CellOut{});
 // With pl.plate set, the backward pass (fbar = lam_next, no ebar) applies
 // the reverse plate step: it writes pl.lam instead of ybar and adds m
 // thetabar to pl.thetabar_acc; the finalize kernel needs y and lam_next.
@@ -211,7 +235,7 @@ hipError_t launch_forward_backward_main(const DeviceTables& T, const DeviceTable
                                         const Range& r, const LaunchCfg& cfg,
                                         const float* y, float* f, const float* fbar,
                                         const double* ebar, float* ybar, hipStream_t st,
-                                        bool grad = true);
+                                        bool grad = true, const CellOut& out = CellOut{});
 hipError_t launch_forward_backward_finalize(const DeviceTables& T, const DeviceTables& Tb,
                                             const Range& r, float* f, double* energy,
                                             int32_t* ninv, float* ybar, double* thetabar,

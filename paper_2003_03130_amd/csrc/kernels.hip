@@ -185,15 +185,8 @@ __global__ __launch_bounds__(256) void forward_finalize_kernel(FinArgs a,
       if (a.nonfin) a.nonfin[c] = cs.nf;
     }
     if (a.pl.force) {
-      const int t0 = a.T.cell_tile_first[c], nt = a.T.cell_tile_count[c];
-      // top-plate force: the tile shares, then the nodes of no tetrahedron
-      double fp = 0.0;
-      for (int k = lane; k < nt; k += 64)
-        fp += a.T.tile_plate[t0 + (int64_t)k * a.T.tile_stride];
-      const float top = (float)a.pl.plate[2 * c];
-      for (int o = a.T.orphan_off[c] + lane; o < a.T.orphan_off[c + 1]; o += 64)
-        fp += plate_top_term(a.y[2 * a.T.n_nodes + a.T.orphan_node[o]], top, a.pl.k);
-      fp = wave_sum(fp);
+      const double fp =
+          cell_plate_force(a.T, c, lane, a.y, (float)a.pl.plate[2 * c], a.pl.k);
       if (lane == 0) a.pl.force[c] = fp;
     }
     return;
@@ -240,13 +233,14 @@ size_t forward_lds_per_wave(int nloc) { return (size_t)28 * nloc; }
 
 hipError_t launch_forward_main(const DeviceTables& T, const Range& r,
                                const LaunchCfg& cfg, const float* y, float* f,
-                               hipStream_t st, const PlateFwd& pl, bool check) {
+                               hipStream_t st, const PlateFwd& pl, bool check,
+                               const CellOut& out) {
   if (r.tile_end <= r.tile_begin) return hipSuccess;
   if (check && !T.tile_nonfin) return hipErrorInvalidValue;
   // the per-wave LDS stride (7 nloc / 4 float4) needs nloc % 4 == 0
   if (T.nloc <= 0 || T.nloc % 4 != 0) return hipErrorInvalidValue;
   if (use_lists(T, r, cfg, true, false, false))
-    return launch_list_forward(T, r, y, f, st, pl, check);
+    return launch_list_forward(T, r, y, f, st, pl, check, out);
   if (const int K = wide_waves(r, cfg, forward_lds_per_wave(T.nloc), false))
     return launch_wide_forward(T, r, K, y, f, st, pl, check);
   FwdArgs a{T, r, y, f, pl, check ? 1 : 0};
@@ -280,8 +274,10 @@ hipError_t launch_forward(const DeviceTables& T, const Range& r,
                           const LaunchCfg& cfg, const float* y, float* f,
                           double* energy, int32_t* ninv, hipStream_t st,
                           const PlateFwd& pl, int32_t* nonfin) {
-  hipError_t e = launch_forward_main(T, r, cfg, y, f, st, pl, nonfin != nullptr);
-  if (e != hipSuccess) return e;
+  const bool tail = use_tail(T, r, cfg, true, false, false);
+  const CellOut out{tail ? T.cell_done : nullptr, energy, ninv, nonfin, nullptr};
+  hipError_t e = launch_forward_main(T, r, cfg, y, f, st, pl, nonfin != nullptr, out);
+  if (e != hipSuccess || tail) return e;
   return launch_forward_finalize(T, r, f, energy, ninv, st, y, pl, nonfin);
 }
 

@@ -18,7 +18,7 @@
 // fill the chip keep the other passes.
 #include <hip/hip_runtime.h>
 
-#include "wide.h"
+#include "tail.h"
 
 namespace cm {
 namespace {
@@ -44,7 +44,7 @@ __device__ __forceinline__ void put_contributions(float* o, const float h[3][3])
                      -(h[0][1] + h[1][1] + h[2][1]), -(h[0][2] + h[1][2] + h[2][2]));
 }
 
-template <int K, bool FWD, bool BWD, bool PL, bool GRAD>
+template <int K, bool FWD, bool BWD, bool PL, bool GRAD, bool TAIL>
 __global__ __launch_bounds__(64 * K) void list_kernel(WideArgs a) {
   extern __shared__ float4 lds[];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -181,7 +181,7 @@ __global__ __launch_bounds__(64 * K) void list_kernel(WideArgs a) {
         }
       }
     }
-    if (l < nl) store_node<FWD, BWD, PL>(a, d, l, fv, gv, ys, vs, top, bot, gw);
+    if (l < nl) store_node<FWD, BWD, PL, TAIL>(a, d, l, fv, gv, ys, vs, top, bot, gw);
   }
   // per-tile sums on the last wavefronts, chunk by chunk on each lane
   if constexpr (FWD) {
@@ -196,15 +196,15 @@ __global__ __launch_bounds__(64 * K) void list_kernel(WideArgs a) {
           ni += cnt[2 * k];
           nf += cnt[2 * k + 1];
         }
-        a.tile_acc[t] = e;
-        a.tile_ninv[t] = ni;
-        if (!BWD && a.check) a.tile_nonfin[t] = nf;
+        store_as<TAIL>(a.tile_acc + t, e);
+        store_as<TAIL>(a.tile_ninv + t, ni);
+        if (!BWD && a.check) store_as<TAIL>(a.tile_nonfin + t, nf);
       }
     }
     if constexpr (PL) {
       if (wave == K - 2) {
         const double fp = plate_share(d, ys, lane, top, a.pf.k);
-        if (lane == 0) a.tile_plate[t] = fp;
+        if (lane == 0) store_as<TAIL>(a.tile_plate + t, fp);
       }
     }
   }
@@ -218,14 +218,15 @@ __global__ __launch_bounds__(64 * K) void list_kernel(WideArgs a) {
         e = fma(v, th[(3 + c) * L + 64 * k + lane], e);
       }
       const double s = wave_sum(fma(0.5 * eb, e, -p));
-      if (lane == 0) a.tile_acc_b[3 * (int64_t)t + c] = s;
+      if (lane == 0) store_as<TAIL>(a.tile_acc_b + 3 * (int64_t)t + c, s);
     }
   }
+  if constexpr (TAIL) cell_tail<64 * K, FWD, BWD, PL, GRAD>(a, d.cell, tid, cnt);
 }
 
-template <int K, bool FWD, bool BWD, bool PL, bool GRAD>
+template <int K, bool FWD, bool BWD, bool PL, bool GRAD, bool TAIL>
 hipError_t list_go(const WideArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL((list_kernel<K, FWD, BWD, PL, GRAD>), dim3(a.n_tiles), dim3(64 * K),
+  hipLaunchKernelGGL((list_kernel<K, FWD, BWD, PL, GRAD, TAIL>), dim3(a.n_tiles), dim3(64 * K),
                      list_lds(a.nloc, a.lists, FWD, BWD, GRAD), st, a);
   return hipGetLastError();
 }
@@ -234,7 +235,8 @@ hipError_t list_go(const WideArgs& a, hipStream_t st) {
 // 13.0 us, adjoint 10.5, 11.4, 11.8).
 template <bool FWD, bool BWD, bool PL, bool GRAD>
 hipError_t list_run(const WideArgs& a, hipStream_t st) {
-  return list_go<16, FWD, BWD, PL, GRAD>(a, st);
+  if (a.out.done) return list_go<16, FWD, BWD, PL, GRAD, true>(a, st);
+  return list_go<16, FWD, BWD, PL, GRAD, false>(a, st);
 }
 
 }  // namespace
@@ -252,9 +254,25 @@ bool use_lists(const DeviceTables& T, const Range& r, const LaunchCfg& cfg, bool
          list_lds(T.nloc, T.lists, fwd, bwd, grad) <= 163840;
 }
 
+// Most shared nodes of a cell for whose sums one workgroup is faster than a
+// finalize launch, finalize -> tail: single passes at 1,512 shared nodes 11.1,
+// 11.4, 11.3 -> 8.9, 10.6, 9.4 us (forward, adjoint, Hessian-vector product), at
+// 2,607 11.0, 11.3, 10.8 -> 10.4, 12.1, 11.4, at 4,820 10.8 -> 14.6; both passes
+// at 331 12.5 -> 11.8, at 1,040 12.0 -> 12.6.  Passes with more than 256 tiles
+// keep the finalize: several workgroups share a CU there, and the arrival of a
+// tile's stores holds up the next tile (forward of 650 tiles 13.9 -> 18.4).
+constexpr int kTailShared = 2048, kTailSharedBoth = 512;
+
+bool use_tail(const DeviceTables& T, const Range& r, const LaunchCfg& cfg, bool fwd, bool bwd,
+              bool grad) {
+  return T.cell_done && r.tile_end > r.tile_begin && use_lists(T, r, cfg, fwd, bwd, grad) &&
+         T.max_cell_shared <= (fwd && bwd ? kTailSharedBoth : kTailShared);
+}
+
 hipError_t launch_list_forward(const DeviceTables& T, const Range& r, const float* y, float* f,
-                               hipStream_t st, const PlateFwd& pl, bool check) {
-  WideArgs a = forward_args(T, r, y, f, pl, check);
+                               hipStream_t st, const PlateFwd& pl, bool check,
+                               const CellOut& out) {
+  WideArgs a = forward_args(T, r, y, f, pl, check, out);
   return pl.plate ? list_run<true, false, true, false>(a, st)
                   : list_run<true, false, false, false>(a, st);
 }
@@ -262,8 +280,8 @@ hipError_t launch_list_forward(const DeviceTables& T, const Range& r, const floa
 hipError_t launch_list_backward(const DeviceTables& T, const Range& r, const float* y,
                                 const float* fbar, const double* ebar, float* ybar,
                                 hipStream_t st, const CellMask& mask, const PlateBwd& pl,
-                                bool grad) {
-  WideArgs a = backward_args(T, r, y, fbar, ebar, ybar, mask, pl);
+                                bool grad, const CellOut& out) {
+  WideArgs a = backward_args(T, r, y, fbar, ebar, ybar, mask, pl, out);
   if (pl.plate)
     return grad ? list_run<false, true, true, true>(a, st)
                 : list_run<false, true, true, false>(a, st);
@@ -274,8 +292,8 @@ hipError_t launch_list_backward(const DeviceTables& T, const Range& r, const flo
 hipError_t launch_list_forward_backward(const DeviceTables& T, const DeviceTables& Tb,
                                         const Range& r, const float* y, float* f,
                                         const float* fbar, const double* ebar, float* ybar,
-                                        hipStream_t st, bool grad) {
-  WideArgs a = forward_backward_args(T, Tb, r, y, f, fbar, ebar, ybar);
+                                        hipStream_t st, bool grad, const CellOut& out) {
+  WideArgs a = forward_backward_args(T, Tb, r, y, f, fbar, ebar, ybar, out);
   return grad ? list_run<true, true, false, true>(a, st)
               : list_run<true, true, false, false>(a, st);
 }

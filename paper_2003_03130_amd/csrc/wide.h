@@ -39,10 +39,12 @@ struct WideArgs {
   int32_t copies;          // tiles per list block (copies of a shared mesh)
   PlateFwd pf;             // used when PL and FWD
   PlateBwd pb;             // used when PL and BWD
+  CellOut out;             // tail.h, with T
+  DeviceTables T;
 };
 
 inline WideArgs wide_args(const DeviceTables& T, const Range& r, const float* y,
-                   const int32_t* ids) {
+                          const int32_t* ids, const CellOut& out = CellOut{}) {
   WideArgs a{};
   a.tiles = T.tiles;
   a.chunks = T.chunks;
@@ -60,12 +62,15 @@ inline WideArgs wide_args(const DeviceTables& T, const Range& r, const float* y,
   a.lists = T.lists;
   a.copies = T.tile_stride;
   a.last_slot = T.n_slots > 0 ? (int32_t)T.n_slots - 1 : 0;
+  a.out = out;
+  a.T = T;
   return a;
 }
 
 inline WideArgs forward_args(const DeviceTables& T, const Range& r, const float* y, float* f,
-                             const PlateFwd& pl, bool check) {
-  WideArgs a = wide_args(T, r, y, pl.plate ? T.slot_node_first : T.slot_node);
+                             const PlateFwd& pl, bool check,
+                             const CellOut& out = CellOut{}) {
+  WideArgs a = wide_args(T, r, y, pl.plate ? T.slot_node_first : T.slot_node, out);
   a.f = f;
   a.part = T.part;
   a.tile_acc = T.tile_acc;
@@ -79,8 +84,9 @@ inline WideArgs forward_args(const DeviceTables& T, const Range& r, const float*
 
 inline WideArgs backward_args(const DeviceTables& T, const Range& r, const float* y,
                               const float* fbar, const double* ebar, float* ybar,
-                              const CellMask& mask, const PlateBwd& pl) {
-  WideArgs a = wide_args(T, r, y, T.slot_node);
+                              const CellMask& mask, const PlateBwd& pl,
+                              const CellOut& out = CellOut{}) {
+  WideArgs a = wide_args(T, r, y, T.slot_node, out);
   if (fbar) a.fbar = fbar;
   a.has_fbar = fbar ? 1 : 0;
   a.ebar = ebar;
@@ -95,8 +101,9 @@ inline WideArgs backward_args(const DeviceTables& T, const Range& r, const float
 
 inline WideArgs forward_backward_args(const DeviceTables& T, const DeviceTables& Tb,
                                       const Range& r, const float* y, float* f,
-                                      const float* fbar, const double* ebar, float* ybar) {
-  WideArgs a = wide_args(T, r, y, T.slot_node);
+                                      const float* fbar, const double* ebar, float* ybar,
+                                      const CellOut& out = CellOut{}) {
+  WideArgs a = wide_args(T, r, y, T.slot_node, out);
   a.f = f;
   a.part = T.part;
   a.tile_acc = T.tile_acc;
@@ -249,7 +256,7 @@ __device__ __forceinline__ void eval_tet(const TetRegs& cur, const float4* ys,
 
 // Output of tile node l with force sum fv and ybar sum gv: an owned node's
 // values (or its plate step), a shared node's slot partials.
-template <bool FWD, bool BWD, bool PL>
+template <bool FWD, bool BWD, bool PL, bool TAIL = false>
 __device__ __forceinline__ void store_node(const WideArgs& a, const TileDesc& d, int l,
                                            const float fv[3], const float gv[3],
                                            const float4* ys, const float2* vs, float top,
@@ -276,7 +283,13 @@ __device__ __forceinline__ void store_node(const WideArgs& a, const TileDesc& d,
       }
     }
   } else {
-    const int64_t s = 3 * ((int64_t)d.shr_begin + l - d.n_own);
+    const int slot = d.shr_begin + l - d.n_own;
+    const int64_t s = 3 * (int64_t)slot;
+    if constexpr (TAIL) {
+      if constexpr (FWD) device_store3(a.part, slot, fv);
+      if constexpr (BWD) device_store3(a.part_b, slot, gv);
+      return;
+    }
     if constexpr (FWD) {
       a.part[s] = fv[0]; a.part[s + 1] = fv[1]; a.part[s + 2] = fv[2];
     }
