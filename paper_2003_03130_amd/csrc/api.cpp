@@ -315,7 +315,10 @@ static int create_from(cm::Prepared& P, const cm::PrepOptions& po,
       T.max_cell_shared = std::max(T.max_cell_shared,
                                    P.cell_shared_off[c + 1] - P.cell_shared_off[c]);
     }
+    for (int64_t c = 0; c < h->n_cells; ++c)
+      T.max_cell_nodes = std::max(T.max_cell_nodes, P.node_off[c + 1] - P.node_off[c]);
     h->Tb.max_cell_shared = T.max_cell_shared;
+    h->Tb.max_cell_nodes = T.max_cell_nodes;
     if (tiles_everywhere && h->n_tiles <= cm::list_tiles()) {
       const int64_t n = h->n_cells * cm::kDoneStride;
       done.assign(2 * n, 0);
@@ -1135,6 +1138,12 @@ int cm_qs_cg_iteration(cm_batch h, const float* y, const double* plate, double k
   // the Hessian-vector product of the cells still in CG (state column 2),
   // tile pass only: owned nodes into ybar, shared nodes as slot partials
   const cm::CellMask mask{state + 2, cm::kQsState};
+  if (cm::use_cg_tail(h->Tb, full_range(h), h->cfg)) {
+    CM_HIP(cm::launch_qs_cg_iteration(h->Tb, full_range(h), h->d_node_off, y, plate, k_plate,
+                                      rel_tol, ybar, x, r, p, Ap, state, minv, mask, stream,
+                                      h->qs_ind));
+    return CM_OK;
+  }
   CM_HIP(cm::launch_backward_main(h->Tb, full_range(h), h->cfg, y, p, nullptr, ybar,
                                   stream, mask, cm::PlateBwd{}, false));
   CM_HIP(cm::launch_qs_cg(h->d_node_off, h->n_nodes, (int32_t)h->n_cells, y, plate,

@@ -64,6 +64,7 @@ struct DeviceTables {
   // the cell's sums itself (tail.h); null where some cell has no tile
   uint32_t* cell_done = nullptr;
   int32_t max_cell_shared = 0;     // most shared nodes of a cell
+  int64_t max_cell_nodes = 0;      // most nodes of a cell
   int64_t n_nodes = 0, n_slots = 0, n_tiles = 0;
   int32_t n_cells = 0;
   int32_t nloc = 0;                // LDS node capacity per wave (multiple of 4)
@@ -175,6 +176,17 @@ hipError_t launch_list_forward_backward(const DeviceTables& T, const DeviceTable
 // Whether a pass over r forms the cells' sums itself.
 bool use_tail(const DeviceTables& T, const Range& r, const LaunchCfg& cfg, bool fwd, bool bwd,
               bool grad);
+
+// A conjugate-gradient iteration whose Hessian-vector product (the pass over the
+// cells with mask) goes on to the cells' updates itself; use_cg_tail: whether
+// there is one for a pass over r.
+bool use_cg_tail(const DeviceTables& T, const Range& r, const LaunchCfg& cfg);
+hipError_t launch_qs_cg_iteration(const DeviceTables& T, const Range& r,
+                                  const int64_t* node_off, const float* y,
+                                  const double* plate, double k, double rel_tol, float* ybar,
+                                  float* x, float* rv, float* p, float* Ap, double* state,
+                                  const float* minv, const CellMask& mask, hipStream_t st,
+                                  const Indenter& ind);
 
 // The two kernels of each pass, separately (for per-kernel timing); with out.done
 // set (use_tail), the first forms the cells' sums too.

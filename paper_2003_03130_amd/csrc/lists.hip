@@ -44,7 +44,7 @@ __device__ __forceinline__ void put_contributions(float* o, const float h[3][3])
                      -(h[0][1] + h[1][1] + h[2][1]), -(h[0][2] + h[1][2] + h[2][2]));
 }
 
-template <int K, bool FWD, bool BWD, bool PL, bool GRAD, bool TAIL>
+template <int K, bool FWD, bool BWD, bool PL, bool GRAD, Tail TAIL>
 __global__ __launch_bounds__(64 * K) void list_kernel(WideArgs a) {
   extern __shared__ float4 lds[];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -181,7 +181,7 @@ __global__ __launch_bounds__(64 * K) void list_kernel(WideArgs a) {
         }
       }
     }
-    if (l < nl) store_node<FWD, BWD, PL, TAIL>(a, d, l, fv, gv, ys, vs, top, bot, gw);
+    if (l < nl) store_node<FWD, BWD, PL, TAIL != kNoTail, (TAIL > kCellSums)>(a, d, l, fv, gv, ys, vs, top, bot, gw);
   }
   // per-tile sums on the last wavefronts, chunk by chunk on each lane
   if constexpr (FWD) {
@@ -196,15 +196,15 @@ __global__ __launch_bounds__(64 * K) void list_kernel(WideArgs a) {
           ni += cnt[2 * k];
           nf += cnt[2 * k + 1];
         }
-        store_as<TAIL>(a.tile_acc + t, e);
-        store_as<TAIL>(a.tile_ninv + t, ni);
-        if (!BWD && a.check) store_as<TAIL>(a.tile_nonfin + t, nf);
+        store_as<TAIL != kNoTail>(a.tile_acc + t, e);
+        store_as<TAIL != kNoTail>(a.tile_ninv + t, ni);
+        if (!BWD && a.check) store_as<TAIL != kNoTail>(a.tile_nonfin + t, nf);
       }
     }
     if constexpr (PL) {
       if (wave == K - 2) {
         const double fp = plate_share(d, ys, lane, top, a.pf.k);
-        if (lane == 0) store_as<TAIL>(a.tile_plate + t, fp);
+        if (lane == 0) store_as<TAIL != kNoTail>(a.tile_plate + t, fp);
       }
     }
   }
@@ -218,13 +218,17 @@ __global__ __launch_bounds__(64 * K) void list_kernel(WideArgs a) {
         e = fma(v, th[(3 + c) * L + 64 * k + lane], e);
       }
       const double s = wave_sum(fma(0.5 * eb, e, -p));
-      if (lane == 0) store_as<TAIL>(a.tile_acc_b + 3 * (int64_t)t + c, s);
+      if (lane == 0) store_as<TAIL != kNoTail>(a.tile_acc_b + 3 * (int64_t)t + c, s);
     }
   }
-  if constexpr (TAIL) cell_tail<64 * K, FWD, BWD, PL, GRAD>(a, d.cell, tid, cnt);
+  if constexpr (TAIL == kCellSums) cell_tail<64 * K, FWD, BWD, PL, GRAD>(a, d.cell, tid, cnt);
+  if constexpr (TAIL > kCellSums) {
+    static_assert(64 * K == kThreads, "threads of a conjugate-gradient iteration");
+    cg_tail<TAIL == kCgSphere>(a, d.cell, tid, cnt, reinterpret_cast<double*>(lds));
+  }
 }
 
-template <int K, bool FWD, bool BWD, bool PL, bool GRAD, bool TAIL>
+template <int K, bool FWD, bool BWD, bool PL, bool GRAD, Tail TAIL>
 hipError_t list_go(const WideArgs& a, hipStream_t st) {
   hipLaunchKernelGGL((list_kernel<K, FWD, BWD, PL, GRAD, TAIL>), dim3(a.n_tiles), dim3(64 * K),
                      list_lds(a.nloc, a.lists, FWD, BWD, GRAD), st, a);
@@ -235,8 +239,8 @@ hipError_t list_go(const WideArgs& a, hipStream_t st) {
 // 13.0 us, adjoint 10.5, 11.4, 11.8).
 template <bool FWD, bool BWD, bool PL, bool GRAD>
 hipError_t list_run(const WideArgs& a, hipStream_t st) {
-  if (a.out.done) return list_go<16, FWD, BWD, PL, GRAD, true>(a, st);
-  return list_go<16, FWD, BWD, PL, GRAD, false>(a, st);
+  if (a.out.done) return list_go<16, FWD, BWD, PL, GRAD, kCellSums>(a, st);
+  return list_go<16, FWD, BWD, PL, GRAD, kNoTail>(a, st);
 }
 
 }  // namespace
@@ -296,6 +300,28 @@ hipError_t launch_list_forward_backward(const DeviceTables& T, const DeviceTable
   WideArgs a = forward_backward_args(T, Tb, r, y, f, fbar, ebar, ybar, out);
   return grad ? list_run<true, true, false, true>(a, st)
               : list_run<true, true, false, false>(a, st);
+}
+
+// Cells of more nodes take the kernel of their own, which holds four nodes a
+// thread or streams them.
+bool use_cg_tail(const DeviceTables& T, const Range& r, const LaunchCfg& cfg) {
+  return T.cell_done && r.tile_end > r.tile_begin &&
+         use_lists(T, r, cfg, false, true, false) && T.max_cell_nodes <= 2 * kThreads;
+}
+
+hipError_t launch_qs_cg_iteration(const DeviceTables& T, const Range& r,
+                                  const int64_t* node_off, const float* y,
+                                  const double* plate, double k, double rel_tol, float* ybar,
+                                  float* x, float* rv, float* p, float* Ap, double* state,
+                                  const float* minv, const CellMask& mask, hipStream_t st,
+                                  const Indenter& ind) {
+  CellOut out;
+  out.done = T.cell_done;
+  WideArgs a = backward_args(T, r, y, p, nullptr, ybar, mask, PlateBwd{}, out);
+  a.cg = cg_args(node_off, T.n_nodes, y, plate, k, rel_tol, ybar, x, rv, p, Ap, state, minv, &T,
+                 ind);
+  return ind.R > 0.0 ? list_go<16, false, true, false, false, kCgSphere>(a, st)
+                        : list_go<16, false, true, false, false, kCgPlates>(a, st);
 }
 
 }  // namespace cm

@@ -19,13 +19,26 @@
 // 9.0 us; of 30 cells of 900 11.0, 11.4, 11.0 -> 8.3, 9.5, 8.6; backpropagation
 // through 40 plate steps of 8 cells 1,440 -> 1,205.
 #pragma once
-#include "finalize.h"
+#include "cg.h"
 #include "wide.h"
 
 namespace cm {
 
-// The tile of cell c is done but for the arrival of its stores; flag: an int of
-// LDS that the tile no longer uses.
+// Whether a tile pass goes on to its cells' sums, or (a Hessian-vector product of
+// the search direction) to their conjugate-gradient iteration.
+enum Tail { kNoTail, kCellSums, kCgPlates, kCgSphere };
+
+// Whether this workgroup's tile is the last of cell c to arrive, uniform over the
+// workgroup.  flag: an int of LDS that the tile no longer uses.
+__device__ __forceinline__ bool last_of_cell(uint32_t* done, int c, uint32_t last, int tid,
+                                             int* flag) {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (tid == 0) *flag = atomicInc(done + (int64_t)kDoneStride * c, last) == last;
+  __syncthreads();
+  return *flag != 0;
+}
+
 template <int L, bool FWD, bool BWD, bool PL, bool GRAD>
 __device__ __forceinline__ void cell_tail(const WideArgs& a, int c, int tid, int* flag) {
   constexpr int W = L / 64;
@@ -37,11 +50,7 @@ __device__ __forceinline__ void cell_tail(const WideArgs& a, int c, int tid, int
   // the slots of the thread's first node, while the stores are on their way
   SharedSlots sl{};
   if (s0 + tid < s1) sl = shared_slots(a.T.shared_rec[s0 + tid], a.T.shared_rec4);
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __syncthreads();
-  if (tid == 0) *flag = atomicInc(a.out.done + (int64_t)kDoneStride * c, last) == last;
-  __syncthreads();
-  if (*flag == 0) return;
+  if (!last_of_cell(a.out.done, c, last, tid, flag)) return;
 
   float top = 0.f, bot = 0.f, gw = 0.f;
   if constexpr (PL) {
@@ -120,6 +129,22 @@ __device__ __forceinline__ void cell_tail(const WideArgs& a, int c, int tid, int
       }
     }
   }
+}
+
+// One conjugate-gradient iteration of cell c (at most 2 kThreads nodes) by the
+// workgroup of its last tile; red: 1 KB of LDS that the tile no longer uses.  An
+// iteration was two launches, each a chain of loads on a few CUs: force curves of
+// 16 cells of 1,900 nodes 48.5 -> 44.4 ms.
+template <bool SPH>
+__device__ __forceinline__ void cg_tail(const WideArgs& a, int c, int tid, int* flag,
+                                        double* red) {
+  const uint32_t last = (uint32_t)a.T.cell_tile_count[c] - 1;
+  const CgArgs& g = a.cg;
+  const int64_t n0 = g.node_off[c], n1 = g.node_off[c + 1];
+  const double top = g.plate[2 * c], bot = g.plate[2 * c + 1];
+  const ShrRange sr = shared_range(g, c, n1);
+  if (!last_of_cell(a.out.done, c, last, tid, flag)) return;
+  cg_step_regs<2, SPH, true>(g, g.st + kQsState * c, c, n0, n1, top, bot, red, sr);
 }
 
 }  // namespace cm

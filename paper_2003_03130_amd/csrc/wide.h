@@ -4,6 +4,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include "cg.h"
 #include "device_util.h"
 #include "kernels.h"
 #include "mr_tet.h"
@@ -41,6 +42,7 @@ struct WideArgs {
   PlateBwd pb;             // used when PL and BWD
   CellOut out;             // tail.h, with T
   DeviceTables T;
+  CgArgs cg;               // tail.h: the iteration that a Hessian product ends in
 };
 
 inline WideArgs wide_args(const DeviceTables& T, const Range& r, const float* y,
@@ -256,7 +258,7 @@ __device__ __forceinline__ void eval_tet(const TetRegs& cur, const float4* ys,
 
 // Output of tile node l with force sum fv and ybar sum gv: an owned node's
 // values (or its plate step), a shared node's slot partials.
-template <bool FWD, bool BWD, bool PL, bool TAIL = false>
+template <bool FWD, bool BWD, bool PL, bool TAIL = false, bool CG = false>
 __device__ __forceinline__ void store_node(const WideArgs& a, const TileDesc& d, int l,
                                            const float fv[3], const float gv[3],
                                            const float4* ys, const float2* vs, float top,
@@ -279,7 +281,8 @@ __device__ __forceinline__ void store_node(const WideArgs& a, const TileDesc& d,
         a.f[g] = fv[0]; a.f[N + g] = fv[1]; a.f[2 * N + g] = fv[2];
       }
       if constexpr (BWD) {
-        a.ybar[g] = gv[0]; a.ybar[N + g] = gv[1]; a.ybar[2 * N + g] = gv[2];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) store_as<CG>(a.ybar + c * N + g, gv[c]);
       }
     }
   } else {
