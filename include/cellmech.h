@@ -629,6 +629,14 @@ int cm_qs_cg_iteration(cm_batch h, const float* y, const double* plate, double k
                        float* Ap, double* state, const float* minv, hipStream_t stream);
 int cm_qs_update(cm_batch h, const float* x, double cap, float* y, double* state,
                  hipStream_t stream);
+/*
+ * cm_qs_any: *flag = 1 if state[c][column] > 0 for some cell, else 0 (a state
+ * column in [0, 16)); flag: device memory, or pinned host memory, which the
+ * host may read once `stream` has reached this call.  CM_EINVAL for a null
+ * pointer or a column out of range.
+ */
+int cm_qs_any(cm_batch h, const double* state, int32_t column, int32_t* flag,
+              hipStream_t stream);
 int cm_qs_predict(cm_batch h, const double* plate_old, const double* plate_new,
                   float* y, hipStream_t stream);
 

@@ -1163,6 +1163,16 @@ int cm_qs_update(cm_batch h, const float* x, double cap, float* y, double* state
   return CM_OK;
 }
 
+int cm_qs_any(cm_batch h, const double* state, int32_t column, int32_t* flag,
+              hipStream_t stream) {
+  if (int rc = check_handle(h)) return rc;
+  if (!state || !flag) return fail(CM_EINVAL, "state and flag must be device-visible pointers");
+  if (column < 0 || column >= cm::kQsState) return fail(CM_EINVAL, "no such state column");
+  if (int rc = select_device(h)) return rc;
+  CM_HIP(cm::launch_qs_any((int32_t)h->n_cells, state + column, flag, stream));
+  return CM_OK;
+}
+
 int cm_qs_predict(cm_batch h, const double* plate_old, const double* plate_new,
                   float* y, hipStream_t stream) {
   if (int rc = check_handle(h)) return rc;

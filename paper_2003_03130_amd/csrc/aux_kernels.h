@@ -100,6 +100,7 @@ hipError_t launch_qs_stiffness(const DeviceTables& T, const Range& r, float* kel
 hipError_t launch_qs_update(const int64_t* node_off, int64_t N, int32_t n_cells,
                             const float* x, double cap, float* y, double* st,
                             hipStream_t s);
+hipError_t launch_qs_any(int32_t n_cells, const double* column, int32_t* flag, hipStream_t s);
 hipError_t launch_qs_predict(const int64_t* node_off, int64_t N, int32_t n_cells,
                              const double* plate_old, const double* plate_new,
                              float* y, hipStream_t s);

@@ -132,20 +132,20 @@ class QuasiStaticCompression:
             _ptr(self._minv), _stream(None)))
 
     def _active(self, col):
-        return bool((self.state[:, col] > 0).any())
+        return self._active_async(col)()
 
     def _active_async(self, col):
         """Queues on the current stream a check whether any cell has state
-        column col set, copied into pinned host memory; returns a function
-        that waits for that copy alone and returns the answer."""
+        column col set, written into pinned host memory; returns a function
+        that waits for that check alone and returns the answer."""
         import torch
         if self._flags is None:
-            self._flags = [torch.zeros(1, dtype=torch.bool, pin_memory=True)
-                           for _ in range(2)]
-        buf = self._flags[self._flag_i]
+            self._flags = [(torch.zeros(1, dtype=torch.int32, pin_memory=True),
+                            torch.cuda.Event()) for _ in range(2)]
+        buf, ev = self._flags[self._flag_i]
         self._flag_i ^= 1
-        buf.copy_((self.state[:, col] > 0).any().reshape(1), non_blocking=True)
-        ev = torch.cuda.Event()
+        nat.check(nat.lib().cm_qs_any(self.cb._h, _ptr(self.state), col, _ptr(buf),
+                                      _stream(None)))
         ev.record()
 
         def wait():
