@@ -911,24 +911,21 @@ bool list_tables(const Prepared& P, ListHost* out) {
   auto vertex = [](const uint32_t* a, int s) {
     return (int)((s & 1) ? a[s >> 1] >> 16 : a[s >> 1] & 0xffff);
   };
-  std::vector<std::vector<uint16_t>> block(n_tiles / copies);
-  std::vector<int32_t> count, order, place, next;
-  for (int64_t t = 0; t < n_tiles; t += copies) {
+  const int64_t n_blocks = n_tiles / copies;
+  std::vector<std::vector<uint16_t>> block(n_blocks);
+  // the block of tile t; false: its records do not fit the 16-bit offsets
+  auto tile_block = [&](int64_t t, std::vector<uint16_t>& o) {
     const TileDesc& d = P.tiles[t];
     const TetChunk* ch = P.chunks.data() + d.chunk_begin;
     const int nl = d.n_own + d.n_shr;
-    count.assign(nl, 0);
+    std::vector<int32_t> count(nl, 0), order(nl), place(nl);
     for (int k = 0; k < d.n_chunks; ++k)
       for (int l = 0; l < kChunk; ++l)
         if (ch[k].a[l][0] != kEmptyLane)
           for (int s = 0; s < 4; ++s) ++count[vertex(ch[k].a[l], s)];
-    order.resize(nl);
     std::iota(order.begin(), order.end(), 0);
     std::stable_sort(order.begin(), order.end(),
                      [&](int32_t a, int32_t b) { return count[a] > count[b]; });
-    place.resize(nl);
-    for (int i = 0; i < nl; ++i) place[order[i]] = i;
-    std::vector<uint16_t>& o = block[t / copies];
     o.assign(n_order + n_lists, 0);
     for (size_t i = 0; i < n_order; ++i) o[i] = i < (size_t)nl ? (uint16_t)order[i] : kNoNode;
     size_t records = 0;
@@ -941,19 +938,35 @@ bool list_tables(const Prepared& P, ListHost* out) {
       records += n;
     }
     o.resize(n_order + n_lists + records * 256, none);
+    // a node's next entry: four in a row, then the next record of its group
+    for (int i = 0; i < nl; ++i)
+      place[order[i]] = o[n_order + 2 * (i / 64)] * 256 + (i % 64) * 4;
     uint16_t* rec = o.data() + n_order + n_lists;
-    next.assign(nl, 0);
     for (int k = 0; k < d.n_chunks; ++k)
       for (int s = 0; s < 4; ++s)
         for (int l = 0; l < kChunk; ++l)
           if (ch[k].a[l][0] != kEmptyLane) {
-            const int i = place[vertex(ch[k].a[l], s)], j = next[i]++;
-            const size_t first = o[n_order + 2 * (i / 64)];
-            rec[(first + j / 4) * 256 + (size_t)(i % 64) * 4 + j % 4] =
-                (uint16_t)(k << 8 | l << 2 | s);
+            int32_t& e = place[vertex(ch[k].a[l], s)];
+            rec[e] = (uint16_t)(k << 8 | l << 2 | s);
+            e += (e & 3) == 3 ? 253 : 1;
           }
+    return true;
+  };
+  std::atomic<int64_t> next_block(0);
+  std::atomic<bool> fits(true);
+  auto work = [&]() {
+    for (int64_t b; (b = next_block.fetch_add(1)) < n_blocks;)
+      if (!tile_block(b * copies, block[b])) fits = false;
+  };
+  const int64_t nt = std::min<int64_t>(
+      std::max(1u, std::min(16u, std::thread::hardware_concurrency())), n_blocks / 8);
+  std::vector<std::thread> pool;
+  for (int64_t i = 1; i < nt; ++i) pool.emplace_back(work);
+  work();
+  for (auto& th : pool) th.join();
+  if (!fits) return false;
+  for (const auto& o : block)
     out->stride16 = std::max(out->stride16, (int32_t)(o.size() / 8));
-  }
   out->blocks.assign(block.size() * (size_t)out->stride16 * 8, 0);
   for (size_t b = 0; b < block.size(); ++b)
     std::copy(block[b].begin(), block[b].end(),
