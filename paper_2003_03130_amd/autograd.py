@@ -17,7 +17,7 @@ class MRForces(torch.autograd.Function):
     @staticmethod
     def forward(ctx, y, theta, batch):
         theta = theta.detach().to(torch.float64).contiguous()
-        batch.set_params(theta[:, 0], theta[:, 1], theta[:, 2])
+        batch._set_theta(theta)
         f, E = batch.forces(y.detach().contiguous())
         ctx.batch = batch
         ctx.save_for_backward(y.detach(), theta)
@@ -28,7 +28,7 @@ class MRForces(torch.autograd.Function):
         y, theta = ctx.saved_tensors
         batch = ctx.batch
         # the handle's parameters may have changed since forward
-        batch.set_params(theta[:, 0], theta[:, 1], theta[:, 2])
+        batch._set_theta(theta)
         gf = grad_f.contiguous().float() if grad_f is not None else None
         gE = grad_E.contiguous().double() if grad_E is not None else None
         ybar, tb = batch.backward(y, gf, gE)

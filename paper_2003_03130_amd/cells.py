@@ -9,20 +9,25 @@ import numpy as np
 from . import _native as nat
 
 
-def _ptr(a) -> ctypes.c_void_p:
+def _ptr(a):
     """Raw pointer of a numpy array or a torch tensor (None -> NULL)."""
     if a is None:
         return None
     if isinstance(a, np.ndarray):
-        return ctypes.c_void_p(a.ctypes.data)
-    return ctypes.c_void_p(a.data_ptr())
+        return a.ctypes.data
+    return a.data_ptr()
 
 
 def _stream(stream):
+    """Raw handle of a torch stream (None: the current one, whose Stream
+    object takes 3 us to make, a third of a small call)."""
     import torch
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None:
+        return torch.cuda.current_stream().cuda_stream
+    return raw(torch.cuda.current_device())
 
 
 def _options(order, tile_tets, degenerate_tol):
@@ -230,6 +235,20 @@ class CellBatch:
             nat.check(nat.lib().cm_set_params(
                 self._h, _ptr(arr[0]), _ptr(arr[1]), _ptr(arr[2]), 0,
                 _stream(stream)))
+
+    def _set_theta(self, theta):
+        """set_params from the columns of a contiguous float64 device tensor
+        (n_mat, 3) without slicing it."""
+        import torch
+        if not (theta.dim() == 2 and theta.shape[0] == self.n_mat and theta.shape[1] == 3
+                and theta.dtype == torch.float64 and theta.device == self.device
+                and theta.is_contiguous()):
+            self.set_params(theta[:, 0], theta[:, 1], theta[:, 2])
+            return
+        self._param_keep = [theta]
+        p = theta.data_ptr()
+        nat.check(nat.lib().cm_set_params_strided(self._h, p, 3, p + 8, 3, p + 16, 3,
+                                                  _stream(None)))
 
     # ------------------------------------------------------------ compute
     def forces(self, y, f=None, energy=None, n_inverted=None, stream=None,
