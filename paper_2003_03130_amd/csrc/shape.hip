@@ -76,7 +76,7 @@ struct MomArgs {
 // One tile's record, by one wavefront with ys for the tile's nodes.  Of the
 // chunks only the indices are read (8 of every 16 bytes of one row, a third
 // of the chunk), two chunks ahead of their use.
-constexpr int kMomWaves = 8;
+constexpr int kMomWaves = 8;  // of the records alone
 
 __device__ __forceinline__ void tile_moments(const MomArgs& a, int t, int lane, float4* ys) {
   const TileDesc d = a.T.tiles[t];
@@ -491,7 +491,6 @@ __device__ __forceinline__ double dist2(double dx, double dy, double dz) {
   return dx * dx + dy * dy + dz * dz;
 }
 
-constexpr int kCellThreads = 64 * kMomWaves;
 constexpr int kGroup = 16;  // nodes that share a bounding box
 
 struct CellArgs {
@@ -504,6 +503,7 @@ struct CellArgs {
 
 // Largest value over the workgroup (v >= 0) on every thread, and one of the
 // places it was found at.
+template <int W>
 __device__ __forceinline__ void cell_argmax(double& v, int& i, double* rv, int* ri) {
   const double m = wave_max(v);
   const int first = __ffsll((long long)__ballot(v == m)) - 1;
@@ -513,7 +513,7 @@ __device__ __forceinline__ void cell_argmax(double& v, int& i, double* rv, int* 
   v = rv[0];
   i = ri[0];
 #pragma unroll
-  for (int w = 1; w < kMomWaves; ++w)
+  for (int w = 1; w < W; ++w)
     if (rv[w] > v) { v = rv[w]; i = ri[w]; }
   __syncthreads();  // rv, ri are used again
 }
@@ -533,10 +533,11 @@ struct Max { __device__ float operator()(float a, float b) const { return fmaxf(
 // lane's node and the box, could be farther apart than the largest distance so
 // far.  All tests keep a relative margin of 1e-12 against the rounding of the
 // sums, so the result is that of all pairs.
+template <int W>
 __device__ __forceinline__ void cell_search(const CellArgs& a, int c, float* sx) {
-  __shared__ double rv[kMomWaves];
-  __shared__ int ri[kMomWaves];
-  __shared__ float rb[kMomWaves][6];
+  __shared__ double rv[W];
+  __shared__ int ri[W];
+  __shared__ float rb[W][6];
   __shared__ unsigned long long best_bits;
   const float* y = a.mom.y;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -545,12 +546,12 @@ __device__ __forceinline__ void cell_search(const CellArgs& a, int c, float* sx)
   const int ns = a.candidates[c];
   float *sy = sx + a.cap, *sz = sy + a.cap, *box = sz + a.cap;
   float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-  for (int b = 0; b < ns; b += 4 * kCellThreads) {  // four gathers in flight
+  for (int b = 0; b < ns; b += 4 * 64 * W) {  // four gathers in flight
     int64_t g[4];
     float p[4][3];
 #pragma unroll
     for (int u = 0; u < 4; ++u)
-      g[u] = a.order[n0 + min(b + u * kCellThreads + tid, ns - 1)];
+      g[u] = a.order[n0 + min(b + u * 64 * W + tid, ns - 1)];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       p[u][0] = y[g[u]];
@@ -564,7 +565,7 @@ __device__ __forceinline__ void cell_search(const CellArgs& a, int c, float* sx)
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const int i = b + u * kCellThreads + tid;
+      const int i = b + u * 64 * W + tid;
       if (i < ns) { sx[i] = p[u][0]; sy[i] = p[u][1]; sz[i] = p[u][2]; }
     }
   }
@@ -579,7 +580,7 @@ __device__ __forceinline__ void cell_search(const CellArgs& a, int c, float* sx)
   for (int d = 0; d < 3; ++d) {
     float l = rb[0][d], h = rb[0][3 + d];
 #pragma unroll
-    for (int w = 1; w < kMomWaves; ++w) {
+    for (int w = 1; w < W; ++w) {
       l = fminf(l, rb[w][d]);
       h = fmaxf(h, rb[w][3 + d]);
     }
@@ -591,11 +592,11 @@ __device__ __forceinline__ void cell_search(const CellArgs& a, int c, float* sx)
   for (int step = 0; step < 4; ++step) {
     double v = 0.0;
     int i = 0;
-    for (int k = tid; k < ns; k += kCellThreads) {
+    for (int k = tid; k < ns; k += 64 * W) {
       const double d2 = dist2(px - sx[k], py - sy[k], pz - sz[k]);
       if (d2 > v) { v = d2; i = k; }
     }
-    cell_argmax(v, i, rv, ri);
+    cell_argmax<W>(v, i, rv, ri);
     if (step == 0) {
       R2 = v;
     } else {
@@ -609,7 +610,7 @@ __device__ __forceinline__ void cell_search(const CellArgs& a, int c, float* sx)
   const double gap = sqrt(L2) * (1.0 - 1e-12) - sqrt(R2) * (1.0 + 1e-12);
   const double least2 = gap > 0.0 ? gap * gap * (1.0 - 1e-12) : 0.0;
   int kept = 0;
-  for (int b = 0; b < ns; b += kCellThreads) {
+  for (int b = 0; b < ns; b += 64 * W) {
     const int k = b + tid;
     float x = 0.f, yk = 0.f, z = 0.f;
     bool keep = false;
@@ -622,7 +623,7 @@ __device__ __forceinline__ void cell_search(const CellArgs& a, int c, float* sx)
     __syncthreads();  // (all positions of this round are in registers)
     int at = kept;
 #pragma unroll
-    for (int w = 0; w < kMomWaves; ++w) {
+    for (int w = 0; w < W; ++w) {
       if (w < wave) at += ri[w];
       kept += ri[w];
     }
@@ -634,7 +635,7 @@ __device__ __forceinline__ void cell_search(const CellArgs& a, int c, float* sx)
   }
   // the last 64 are filled up with the last node, then the boxes
   const int blocks = (kept + 63) / 64;
-  for (int b = wave; b < blocks; b += kMomWaves) {
+  for (int b = wave; b < blocks; b += W) {
     const int k = 64 * b + lane, from = min(k, kept - 1);
     const float v[3] = {sx[from], sy[from], sz[from]};
     wave_sync();
@@ -656,7 +657,7 @@ __device__ __forceinline__ void cell_search(const CellArgs& a, int c, float* sx)
   for (int g = 0; g < blocks; ++g)
     for (int h0 = g * (64 / kGroup); h0 < groups; h0 += 64) {
       const bool mine = turn == wave;
-      turn = turn + 1 == kMomWaves ? 0 : turn + 1;
+      turn = turn + 1 == W ? 0 : turn + 1;
       if (!mine) continue;
       const double best0 = __longlong_as_double((long long)__hip_atomic_load(
           &best_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
@@ -707,16 +708,17 @@ __device__ __forceinline__ void cell_search(const CellArgs& a, int c, float* sx)
 // tile records, a wavefront per tile.  Both are bound by their chains of
 // dependent loads, which overlap here; six launches in a row before (records,
 // extreme nodes, boxes, pairs of blocks of 256, all pairs of inverted cells,
-// fields).  512 cells of 1,000 to 9,000 nodes, 5 M tets: 131 -> 42 us for
-// cm_shape, of which 33 here and 9 in shape_cell_kernel (its eigenvalues are a
+// fields).  512 cells of 1,000 to 9,000 nodes, 5 M tets: 131 -> 38 us for
+// cm_shape, of which 29 here and 9 in shape_cell_kernel (its eigenvalues are a
 // chain of divisions and square roots); 64 cells of 20,000 nodes 200 -> 42, one
-// of 1,000 nodes 43 -> 14; 1,024 equal spheres of 2,000 nodes, where every
-// candidate remains, 189 -> 141.
-__global__ __launch_bounds__(kCellThreads) void shape_pass_kernel(CellArgs a) {
+// of 1,000 nodes 43 -> 13; 1,024 equal spheres of 2,000 nodes, where every
+// candidate remains, 189 -> 123.
+template <int W>
+__global__ __launch_bounds__(64 * W) void shape_pass_kernel(CellArgs a) {
   extern __shared__ float4 lds[];
   const int nc = a.mom.T.n_cells;
   if ((int)blockIdx.x < nc) {
-    cell_search(a, blockIdx.x, reinterpret_cast<float*>(lds));
+    cell_search<W>(a, blockIdx.x, reinterpret_cast<float*>(lds));
     return;
   }
   const int lane = threadIdx.x & 63;
@@ -763,18 +765,28 @@ hipError_t launch_shape(const DeviceTables& T, const int64_t* node_off,
                         double* out, hipStream_t st) {
   const int nc = T.n_cells;
   hipError_t e;
-  // (the caller checks that one tile fits 64 KB; of large tiles a workgroup
-  // takes one)
+  // Wavefronts of a workgroup: four unless the search takes more than 32 KB of
+  // LDS (2,300 candidates), which the records' workgroups beside it are given
+  // too; then eight fill a CU better.  Eight -> four: 512 uneven cells of up to
+  // 2,140 candidates 40.7 -> 38.2 us, 1,024 cells of 2,000 nodes 61.5 -> 54.6; 64
+  // cells of 3,670 candidates 41.5 -> 47.0.
+  const int waves = S.cell_nodes > 0 && cell_lds(S.cell_nodes) <= 32768 ? 4 : kMomWaves;
+  // (the caller checks that one tile fits 64 KB; a workgroup takes as many tiles
+  // as do)
   const int per =
-      std::min(kMomWaves, std::max(1, (int)(65536 / std::max<size_t>(shape_lds(T.nloc), 1))));
+      std::min(waves, std::max(1, (int)(65536 / std::max<size_t>(shape_lds(T.nloc), 1))));
   const MomArgs m{T, node_off, y, S.mom, S.tile_inv, S.chunk_neg, per};
   const unsigned mom_blocks = (unsigned)((T.n_tiles + per - 1) / per);
   const size_t mom_lds = per * shape_lds(T.nloc);
   const ShapeFinArgs f{T, node_off, y, S.mom, S.d2max, d_ref, out};
   if (S.cell_nodes > 0) {
     const CellArgs a{m, S.order, S.candidates, S.d2max, S.cell_nodes};
-    hipLaunchKernelGGL(shape_pass_kernel, dim3(nc + mom_blocks), dim3(kCellThreads),
-                       std::max(mom_lds, cell_lds(S.cell_nodes)), st, a);
+    const size_t lds = std::max(mom_lds, cell_lds(S.cell_nodes));
+    if (waves == 4)
+      hipLaunchKernelGGL(shape_pass_kernel<4>, dim3(nc + mom_blocks), dim3(256), lds, st, a);
+    else
+      hipLaunchKernelGGL(shape_pass_kernel<kMomWaves>, dim3(nc + mom_blocks),
+                         dim3(64 * kMomWaves), lds, st, a);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL(shape_cell_kernel, dim3(nc), dim3(256), 0, st, f,
                        (const int32_t*)S.tile_inv);
