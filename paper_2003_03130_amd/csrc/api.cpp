@@ -802,8 +802,9 @@ static std::string device_key(cm_batch h) {
 }
 
 // Names what a cached timing measured (one fused forward + backward
-// evaluation), so that entries timed with another objective are not reused.
-static const char* const kTuneObjective = "|fused-fwd-bwd";
+// evaluation, by these tile passes), so that entries timed with another
+// objective or older passes are not reused.
+static const char* const kTuneObjective = "|fused-fwd-bwd|lists-wide";
 
 static std::string sanitize_key(std::string key) {
   for (char& ch : key)
