@@ -76,6 +76,7 @@ extern "C" int cm_forces_noalloc(cm_batch h, const float* y, float* f,
   CM_HIP(scratch_address(h->device, &base));
   unsigned char* b = static_cast<unsigned char*>(base);
   cm::DeviceTables T = h->T;  // same read-only tables, scratch replaced
+  T.cell_done = nullptr;      // (the handle's counters: a cm_forces may run beside)
   T.part = reinterpret_cast<float*>(b);
   T.tile_acc = reinterpret_cast<double*>(b + off_acc);
   T.tile_ninv = reinterpret_cast<int32_t*>(b + off_ninv);

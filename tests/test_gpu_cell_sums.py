@@ -4,7 +4,8 @@ up to 512) on the GPU: every output bit for bit that of the one-wavefront
 passes with their finalize launch (cm_set_launch), for cells on both sides of
 those limits, uneven cells in one batch, nodes of no tetrahedron, material
 regions, inactive cells, per-cell launches, and over repeated calls with a
-forward and a backward side by side on two streams."""
+forward and a backward, or a forward and one without the handle's scratch, side
+by side on two streams."""
 import numpy as np
 import pytest
 
@@ -86,6 +87,8 @@ def test_inactive_cells_and_percell_launches():
 def test_repeated_calls_beside_each_other():
     import torch
     from paper_2003_03130_amd import CellBatch
+    from paper_2003_03130_amd import _native as nat
+    from paper_2003_03130_amd.cells import _ptr, _stream
     c = small_sphere_case(1002)
     cb = CellBatch.template(6, c.x, c.tets, tile_tets=256)
     assert cb.info["n_tiles"] <= 256
@@ -98,14 +101,22 @@ def test_repeated_calls_beside_each_other():
     cb.set_launch(1, 0)
     torch.cuda.synchronize()
     sides = [torch.cuda.Stream() for _ in range(2)]
-    outs = []
-    for _ in range(100):
-        with torch.cuda.stream(sides[0]):
-            a = cb.forces(y)
-        with torch.cuda.stream(sides[1]):
-            b = cb.backward(y, fb)
-        outs.append((*a, *b))
-    torch.cuda.synchronize()
-    for o in outs:
-        for got, want in zip(o, (f, E, yb, tb)):
-            assert torch.equal(got, want)
+
+    def noalloc():
+        g, e = torch.empty_like(f), torch.empty_like(E)
+        nat.check(nat.lib().cm_forces_noalloc(cb._h, _ptr(y), _ptr(g), _ptr(e), None,
+                                              _stream(None)))
+        return g, e
+
+    for beside, want in ((lambda: cb.backward(y, fb), (yb, tb)), (noalloc, (f, E))):
+        outs = []
+        for _ in range(100):
+            with torch.cuda.stream(sides[0]):
+                a = cb.forces(y)
+            with torch.cuda.stream(sides[1]):
+                b = beside()
+            outs.append((*a, *b))
+        torch.cuda.synchronize()
+        for o in outs:
+            for got, w in zip(o, (f, E, *want)):
+                assert torch.equal(got, w)
