@@ -58,9 +58,10 @@ FUSED_BYTES = (56, 48)  # one tet stream; y, fbar in + f, ybar out per node
 # indices: 8 + 36 + 4), the other denominator reported beside the canonical.
 STORED_TET_BYTES = 48
 F_TOL, E_TOL, G_TOL = 1e-5, 1e-6, 1e-5
-TILE_KERNEL_SOURCES = ("kernels.hip", "backward.hip", "fused.hip",
-                       "device_util.h", "finalize.h", "kernels.h", "layout.h",
-                       "mr_tet.h", "prep.cpp", "util.hip")
+TILE_KERNEL_SOURCES = ("kernels.hip", "backward.hip", "fused.hip", "wide.hip",
+                       "wide.h", "lists.hip", "tail.h", "cg.h", "device_util.h",
+                       "finalize.h", "kernels.h", "layout.h", "mr_tet.h",
+                       "prep.cpp", "util.hip")
 
 
 def kernel_source_hash():

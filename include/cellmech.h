@@ -620,8 +620,9 @@ int cm_qs_cg_step(cm_batch h, const float* y, const double* plate, double k_plat
  * ybar (device float32[3 n_nodes], caller-owned scratch) and leaves the
  * shared nodes' partials in the handle's backward scratch, whose sums the CG
  * kernel forms itself in the finalize's order (one launch and one pass over
- * the shared nodes fewer per iteration).  Uses the backward scratch (do not
- * overlap with cm_forces_backward*).  Errors: as cm_qs_cg_step, CM_ESTATE
+ * the shared nodes fewer per iteration); in batches of up to 256 tiles with at
+ * most 2,048 nodes a cell the tile pass makes the cells' updates too.  Uses
+ * the backward scratch (do not overlap with cm_forces_backward*).  Errors: as cm_qs_cg_step, CM_ESTATE
  * before cm_set_params, CM_EINVAL for a launch beyond the LDS.
  */
 int cm_qs_cg_iteration(cm_batch h, const float* y, const double* plate, double k_plate,

@@ -208,8 +208,9 @@ __device__ __forceinline__ void cg_finish(const CgArgs& a, double* s, double rn,
 // difference).  DEVICE: ybar and the partials were written in this launch
 // (tail.h).
 template <int R, bool SPH, bool DEVICE = false>
-__device__ __forceinline__ void cg_step_regs(const CgArgs& a, double* s, int c, int64_t n0, int64_t n1,
-                             double top, double bot, double* red, const ShrRange& sr) {
+__device__ __forceinline__ void cg_step_regs(const CgArgs& a, double* s, int c, int64_t n0,
+                                             int64_t n1, double top, double bot,
+                                             double* red, const ShrRange& sr) {
   constexpr int kRegNodes = R;
   const int64_t N = a.N;
   float p[kRegNodes][3], r[kRegNodes][3], ap[kRegNodes][3], x[kRegNodes][3];

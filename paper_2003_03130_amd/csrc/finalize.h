@@ -42,7 +42,8 @@ __device__ __forceinline__ double cell_plate_force(const DeviceTables& T, int c,
                                                    const float* y, float top, float k) {
   const int t0 = T.cell_tile_first[c], nt = T.cell_tile_count[c];
   double fp = 0.0;
-  for (int i = lane; i < nt; i += 64) fp += load_as<DEVICE>(T.tile_plate + t0 + (int64_t)i * T.tile_stride);
+  for (int i = lane; i < nt; i += 64)
+    fp += load_as<DEVICE>(T.tile_plate + t0 + (int64_t)i * T.tile_stride);
   for (int o = T.orphan_off[c] + lane; o < T.orphan_off[c + 1]; o += 64)
     fp += plate_top_term(y[2 * T.n_nodes + T.orphan_node[o]], top, k);
   return wave_sum(fp);

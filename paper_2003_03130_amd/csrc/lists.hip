@@ -13,7 +13,8 @@
 // same.  What remains is the evaluation at the issue rate of one CU and the
 // loads before it: at 156 tiles (2,054-node cells, a call with its finalize)
 // forward 11.4 -> 10.1 us, adjoint 12.0 -> 10.5, Hessian-vector product 11.2 ->
-// 9.9, both passes 14.8 -> 12.1.  The lists cost 8 bytes per tetrahedron and the LDS holds
+// 9.9, both passes 14.8 -> 12.1; with the cells' sums formed in the pass (tail.h)
+// forward 8.6, adjoint 9.9, product 9.1.  The lists cost 8 bytes per tetrahedron and the LDS holds
 // one tile per CU in the passes with a parameter gradient, so launches that
 // fill the chip keep the other passes.
 #include <hip/hip_runtime.h>
@@ -181,7 +182,9 @@ __global__ __launch_bounds__(64 * K) void list_kernel(WideArgs a) {
         }
       }
     }
-    if (l < nl) store_node<FWD, BWD, PL, TAIL != kNoTail, (TAIL > kCellSums)>(a, d, l, fv, gv, ys, vs, top, bot, gw);
+    if (l < nl)
+      store_node<FWD, BWD, PL, TAIL != kNoTail, (TAIL > kCellSums)>(a, d, l, fv, gv, ys, vs,
+                                                                    top, bot, gw);
   }
   // per-tile sums on the last wavefronts, chunk by chunk on each lane
   if constexpr (FWD) {

