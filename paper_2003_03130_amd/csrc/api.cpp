@@ -309,17 +309,15 @@ static int create_from(cm::Prepared& P, const cm::PrepOptions& po,
     h->Tb.tile_nonfin = nullptr;
     // arrival counters of the passes that form the cells' sums themselves, one
     // set for either direction (they may run beside each other)
-    bool tiles_everywhere = true;
+    // (every cell has a tile)
     for (int64_t c = 0; c < h->n_cells; ++c) {
-      tiles_everywhere = tiles_everywhere && P.cell_tile_count[c] > 0;
       T.max_cell_shared = std::max(T.max_cell_shared,
                                    P.cell_shared_off[c + 1] - P.cell_shared_off[c]);
-    }
-    for (int64_t c = 0; c < h->n_cells; ++c)
       T.max_cell_nodes = std::max(T.max_cell_nodes, P.node_off[c + 1] - P.node_off[c]);
+    }
     h->Tb.max_cell_shared = T.max_cell_shared;
     h->Tb.max_cell_nodes = T.max_cell_nodes;
-    if (tiles_everywhere && h->n_tiles <= cm::list_tiles()) {
+    if (h->n_tiles <= cm::list_tiles()) {
       const int64_t n = h->n_cells * cm::kDoneStride;
       done.assign(2 * n, 0);
       if ((rc = h->upload(&T.cell_done, done, stream))) return bail(rc);

@@ -61,7 +61,7 @@ struct DeviceTables {
   int32_t* tile_nonfin = nullptr;  // per tile: tets with a non-finite energy
                                    // or force (written by checked passes)
   // per cell, kDoneStride apart: tiles that have arrived in a pass that forms
-  // the cell's sums itself (tail.h); null where some cell has no tile
+  // the cell's sums itself (tail.h); null beyond list_tiles()
   uint32_t* cell_done = nullptr;
   int32_t max_cell_shared = 0;     // most shared nodes of a cell
   int64_t max_cell_nodes = 0;      // most nodes of a cell
