@@ -152,10 +152,10 @@ static int create_from(cm::Prepared& P, const cm::PrepOptions& po,
     shared_cell.assign(n_shr, 0);
     orphan_off.assign(h->n_cells + 1, 0);
     slot_first.assign(P.slot_node.begin(), P.slot_node.end());
+    for (int64_t c = 0; c < h->n_cells; ++c)
+      std::fill(shared_cell.begin() + P.cell_shared_off[c],
+                shared_cell.begin() + P.cell_shared_off[c + 1], (int32_t)c);
     for (size_t s = 0; s < n_shr; ++s) {
-      shared_cell[s] = (int32_t)(std::upper_bound(P.node_off.begin(), P.node_off.end(),
-                                                  (int64_t)P.shared_node[s]) -
-                                 P.node_off.begin() - 1);
       if (P.shared_slot_ptr[s] < P.shared_slot_ptr[s + 1])
         slot_first[P.shared_slots[P.shared_slot_ptr[s]]] |= INT32_MIN;
       else
@@ -171,6 +171,7 @@ static int create_from(cm::Prepared& P, const cm::PrepOptions& po,
     }
     // the slots of every shared node (SharedSlots, finalize.h)
     rec.resize(n_shr);
+    rec4.reserve(n_shr / 4);
     for (size_t s = 0; s < n_shr; ++s) {
       const int32_t* q = P.shared_slots.data() + P.shared_slot_ptr[s];
       const int n = P.shared_slot_ptr[s + 1] - P.shared_slot_ptr[s];
