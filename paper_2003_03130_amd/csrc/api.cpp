@@ -135,7 +135,7 @@ static int create_from(cm::Prepared& P, const cm::PrepOptions& po,
   std::vector<int32_t> shared_cell, orphan_off, orphan, slot_first, shared_first;
   std::vector<int4> pc, rec, rec4;
   std::vector<int32_t> more, cand;
-  std::vector<uint32_t> done;
+  std::vector<uint32_t> done, searched;
   cm::ListHost lists;
   std::vector<int2> nbk;
   {
@@ -262,6 +262,7 @@ static int create_from(cm::Prepared& P, const cm::PrepOptions& po,
     cm::ShapeTables& S = h->shape;
     if (most_cand <= cm::kCellNodes) {
       S.cell_nodes = (most_cand + 63) & ~63;
+      S.helpers = cm::search_helpers(h->n_cells, most_cand);
     } else {
       // 256 x 256 node-pair blocks of every cell (row block <= column block);
       // the cell's nodes are ordered candidates first, so the pairs of the
@@ -290,6 +291,12 @@ static int create_from(cm::Prepared& P, const cm::PrepOptions& po,
         (rc = h->alloc(&S.cell_inv, (size_t)h->n_cells)) ||
         (rc = h->alloc(&S.d2max, (size_t)h->n_cells)))
       return bail(rc);
+    if (S.helpers > 0) {
+      searched.assign(h->n_cells * cm::kDoneStride, 0);
+      if ((rc = h->alloc(&S.rest, (size_t)h->n_cells)) ||
+          (rc = h->upload(&S.done, searched, stream)))
+        return bail(rc);
+    }
     S.cand_blocks = pcd;
     S.n_cand_blocks = (int64_t)pc.size();
     S.chunk_neg = cneg;

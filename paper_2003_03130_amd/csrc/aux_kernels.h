@@ -4,6 +4,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 
 #include "kernels.h"
@@ -17,6 +18,28 @@ constexpr int kShapeFields = 10;
 // Most candidates of a cell for the search by one workgroup, which keeps them in
 // LDS (with their boxes 55 KB).
 constexpr int kCellNodes = 4096;
+// The workgroup that searches a cell compares alone the pairs of up to kSearchNodes
+// remaining nodes, or of an eighth of the candidates if that is more; those of more
+// (near-spherical cells, where all remain) it leaves to `helpers` further workgroups
+// of shape_cell_kernel.  0: none, each takes all of its cell, in handles
+// without such cells and beyond 256 cells, whose searches fill the chip.
+// Equal spheres, alone -> with helpers, and by the block search: 1 cell of 2,000
+// nodes 47 -> 22 us (46), of 9,000 185 -> 41 (54), of 20,000 334 -> 64 (68); 64 cells
+// of 2,000 48 -> 25 (58), of 20,000 343 -> 158 (222); 256 of 9,000 197 -> 173 (259).
+// Ellipsoids, of which a few nodes remain, pay 0.1 to 0.5 us of 14 to 37.  The line:
+// noisy spheres with 250 to 500 nodes left, 64 cells of 2,000 nodes 43 alone, 26
+// shared; but with 293 of 3,670 candidates left, which every helper loads again, 64
+// cells of 20,000 nodes 41 alone, 60 shared.
+constexpr int kSearchNodes = 256;
+inline int search_helpers(int64_t n_cells, int most_candidates) {
+  if (most_candidates <= kSearchNodes || most_candidates > kCellNodes || n_cells > 256) return 0;
+  return (int)std::min<int64_t>(32, 1024 / n_cells);
+}
+// What such a search leaves: the nodes at least sqrt(least2) from the centre.
+struct SearchRest {
+  double centre[3], least2;
+  int32_t left;  // whether it left any
+};
 // Tables and scratch of a handle's shape diagnostics.  cell_nodes: the
 // room of the search of one workgroup per cell, or 0 where some cell has more
 // than kCellNodes candidates; then the block search's tables are there: node
@@ -37,7 +60,11 @@ struct ShapeTables {
   int32_t* tile_inv = nullptr;          // per tile
   int32_t* cell_inv = nullptr;          // per cell (block search)
   double* bbox = nullptr;
-  unsigned long long* d2max = nullptr;  // per cell (block search)
+  unsigned long long* d2max = nullptr;  // per cell
+  int32_t helpers = 0;                  // search_helpers of the handle
+  SearchRest* rest = nullptr;           // per cell (helpers > 0)
+  uint32_t* done = nullptr;             // per cell, kDoneStride apart: workgroups
+                                        // of the cell that have arrived
 };
 size_t shape_lds(int nloc);
 hipError_t launch_shape(const DeviceTables& T, const int64_t* node_off,

@@ -58,6 +58,18 @@ __device__ __forceinline__ T load_as(const T* p) {
   return *p;
 }
 
+// Whether this workgroup is the last of `last` + 1 that count themselves in on
+// *done, uniform over the workgroup; what they stored with device scope has then
+// arrived.  The counter is zero again after the last.  flag: an int of LDS that
+// nothing else uses any more.
+__device__ __forceinline__ bool last_arrival(uint32_t* done, uint32_t last, int tid, int* flag) {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (tid == 0) *flag = atomicInc(done, last) == last;
+  __syncthreads();
+  return *flag != 0;
+}
+
 // One lane's tetrahedron of a chunk: packed local indices, B and V0.
 struct TetRegs {
   uint2 q;

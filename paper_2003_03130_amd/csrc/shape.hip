@@ -15,7 +15,8 @@
 //   shape_cell_kernel     one wavefront per cell: the tile records summed in a
 //                         fixed order, the inertia tensor about the centre of
 //                         mass, its eigenvalues by cyclic Jacobi rotations,
-//                         semi-axes, D, and the strain.
+//                         semi-axes, D, and the strain; beside them the rest of
+//                         the search of cells that left it to more workgroups.
 // The farthest two nodes are convex-hull vertices, and a node whose faces are
 // all shared by two tetrahedra on opposite sides lies inside the image of its
 // star while those keep their orientation (their solid angles at the node sum
@@ -499,6 +500,9 @@ struct CellArgs {
   const int32_t* candidates;  // per cell: how many of them are candidates
   unsigned long long* d2max;
   int32_t cap;                // nodes that the LDS holds (multiple of 64)
+  int32_t helpers;            // as in ShapeTables, with rest and done
+  SearchRest* rest;
+  uint32_t* done;
 };
 
 // Largest value over the workgroup (v >= 0) on every thread, and one of the
@@ -521,31 +525,32 @@ __device__ __forceinline__ void cell_argmax(double& v, int& i, double* rv, int* 
 struct Min { __device__ float operator()(float a, float b) const { return fminf(a, b); } };
 struct Max { __device__ float operator()(float a, float b) const { return fmaxf(a, b); } };
 
-// The largest squared distance of two candidates of cell c, by one workgroup.
-// The candidates' positions are kept in LDS.  From the node farthest from the
-// centre of their box (at distance R), three steps to the node farthest from
-// the last one give a pair whose distance L is a lower bound of d_max, mostly
-// d_max itself.  A node nearer to the centre than L - R has no partner at L or
-// more: the others, in order, are what remains (a few at the tips of an
-// elongated cell, a ring of a flat one, all of a sphere).  They are compact in
-// groups of 16 (Morton order), each with its bounding box: a wavefront takes 64
-// of them, one per lane, and goes over a group only if the boxes, and then some
-// lane's node and the box, could be farther apart than the largest distance so
-// far.  All tests keep a relative margin of 1e-12 against the rounding of the
-// sums, so the result is that of all pairs.
+// The largest squared distance of two candidates of a cell.  The candidates'
+// positions are kept in LDS.  From the node farthest from the centre of their box
+// (at distance R), three steps to the node farthest from the last one give a pair
+// whose distance L is a lower bound of d_max, mostly d_max itself.  A node nearer
+// to the centre than L - R has no partner at L or more: the others, in order, are
+// what remains (a few at the tips of an elongated cell, a ring of a flat one, all
+// of a sphere).  They are compact in groups of 16 (Morton order), each with its
+// bounding box: a wavefront takes 64 of them, one per lane, and goes over a group
+// only if the boxes, and then some lane's node and the box, could be farther
+// apart than the largest distance so far.  All tests keep a relative margin of
+// 1e-12 against the rounding of the sums, so the result is that of all pairs.
+
+// The candidates of cell c into LDS (no barrier); this thread's part of their box.
 template <int W>
-__device__ __forceinline__ void cell_search(const CellArgs& a, int c, float* sx) {
-  __shared__ double rv[W];
-  __shared__ int ri[W];
-  __shared__ float rb[W][6];
-  __shared__ unsigned long long best_bits;
+__device__ __forceinline__ void load_candidates(const CellArgs& a, int c, float* sx,
+                                                float (&lo)[3], float (&hi)[3]) {
   const float* y = a.mom.y;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tid = threadIdx.x;
   const int64_t n0 = a.mom.node_off[c], N = a.mom.T.n_nodes;
   const int ns = a.candidates[c];
-  float *sy = sx + a.cap, *sz = sy + a.cap, *box = sz + a.cap;
-  float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
+  float *sy = sx + a.cap, *sz = sy + a.cap;
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    lo[d] = INFINITY;
+    hi[d] = -INFINITY;
+  }
   for (int b = 0; b < ns; b += 4 * 64 * W) {  // four gathers in flight
     int64_t g[4];
     float p[4][3];
@@ -569,6 +574,136 @@ __device__ __forceinline__ void cell_search(const CellArgs& a, int c, float* sx)
       if (i < ns) { sx[i] = p[u][0]; sy[i] = p[u][1]; sz[i] = p[u][2]; }
     }
   }
+}
+
+// The nodes at least sqrt(least2) from (cx, cy, cz), in place and in order; how
+// many they are.  ri: W ints of LDS.
+template <int W>
+__device__ __forceinline__ int keep_far_nodes(const CellArgs& a, int ns, float* sx, double cx,
+                                              double cy, double cz, double least2, int* ri) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  float *sy = sx + a.cap, *sz = sy + a.cap;
+  int kept = 0;
+  for (int b = 0; b < ns; b += 64 * W) {
+    const int k = b + tid;
+    float x = 0.f, yk = 0.f, z = 0.f;
+    bool keep = false;
+    if (k < ns) {
+      x = sx[k]; yk = sy[k]; z = sz[k];
+      keep = !(dist2(x - cx, yk - cy, z - cz) < least2);
+    }
+    const unsigned long long m = __ballot(keep);
+    if (lane == 0) ri[wave] = __popcll(m);
+    __syncthreads();  // (all positions of this round are in registers)
+    int at = kept;
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+      if (w < wave) at += ri[w];
+      kept += ri[w];
+    }
+    if (keep) {
+      at += __popcll(m & ((1ull << lane) - 1));
+      sx[at] = x; sy[at] = yk; sz[at] = z;
+    }
+    __syncthreads();  // ri is used again
+  }
+  return kept;
+}
+
+// The largest squared distance of two of the `kept` nodes into *best_bits (LDS),
+// from L2 on: of the blocks of 64 rows against 16 column groups, every `stride`-th
+// from first + wave on.  Called by all threads; ends with a barrier.
+template <int W>
+__device__ __forceinline__ void search_pairs(const CellArgs& a, float* sx, int kept, double L2,
+                                             int first, int stride,
+                                             unsigned long long* best_bits) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  float *sy = sx + a.cap, *sz = sy + a.cap, *box = sz + a.cap;
+  // the last 64 are filled up with the last node, then the boxes
+  const int blocks = (kept + 63) / 64;
+  for (int b = wave; b < blocks; b += W) {
+    const int k = 64 * b + lane, from = min(k, kept - 1);
+    const float v[3] = {sx[from], sy[from], sz[from]};
+    wave_sync();
+    if (k >= kept) { sx[k] = v[0]; sy[k] = v[1]; sz[k] = v[2]; }
+    float* to = box + 6 * (k / kGroup);
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      const float lo = row_reduce(v[d], Min()), hi = row_reduce(v[d], Max());
+      if ((lane & 15) == 0) { to[d] = lo; to[3 + d] = hi; }
+    }
+  }
+  if (tid == 0) *best_bits = (unsigned long long)__double_as_longlong(L2);
+  __syncthreads();
+  double best = L2;  // per lane
+  constexpr int kRows = 64 / kGroup;  // groups of a block's rows
+  const int groups = blocks * kRows;
+  int turn = 0;
+  for (int g = 0; g < blocks; ++g)
+    for (int h0 = g * kRows; h0 < groups; h0 += kGroup) {
+      const bool mine = turn == first + wave;
+      turn = turn + 1 == stride ? 0 : turn + 1;
+      if (!mine) continue;
+      const double best0 = __longlong_as_double((long long)__hip_atomic_load(
+          best_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+      best = fmax(best, best0);
+      // a lane per pair of a row group and a column group
+      bool near = false;
+      if (h0 + (lane & 15) < groups) {
+        const float* r = box + 6 * (g * kRows + (lane >> 4));
+        const float* q = box + 6 * (h0 + (lane & 15));
+        const double ex = fmax((double)r[3] - q[0], (double)q[3] - r[0]),
+                     ey = fmax((double)r[4] - q[1], (double)q[4] - r[1]),
+                     ez = fmax((double)r[5] - q[2], (double)q[5] - r[2]);
+        near = !(dist2(ex, ey, ez) < best0 * (1.0 - 1e-12));
+      }
+      const unsigned long long m = __ballot(near);
+      const double x = sx[64 * g + lane], yk = sy[64 * g + lane], z = sz[64 * g + lane];
+      for (uint32_t todo = (uint32_t)(m | m >> 16 | m >> 32 | m >> 48) & 0xffffu; todo != 0;
+           todo &= todo - 1) {
+        const int h = h0 + __ffs((int)todo) - 1;
+        const float* q = box + 6 * h;
+        const double ex = fmax(x - q[0], q[3] - x), ey = fmax(yk - q[1], q[4] - yk),
+                     ez = fmax(z - q[2], q[5] - z);
+        if (__ballot(!(dist2(ex, ey, ez) < best * (1.0 - 1e-12))) == 0) continue;
+        const float4* vx = reinterpret_cast<const float4*>(sx + kGroup * h);
+        const float4* vy = reinterpret_cast<const float4*>(sy + kGroup * h);
+        const float4* vz = reinterpret_cast<const float4*>(sz + kGroup * h);
+#pragma unroll
+        for (int j = 0; j < kGroup / 4; ++j) {
+          const float4 u = vx[j], v = vy[j], w = vz[j];
+          best = fmax(best, dist2(x - u.x, yk - v.x, z - w.x));
+          best = fmax(best, dist2(x - u.y, yk - v.y, z - w.y));
+          best = fmax(best, dist2(x - u.z, yk - v.z, z - w.z));
+          best = fmax(best, dist2(x - u.w, yk - v.w, z - w.w));
+        }
+      }
+      // the maximum of non-negative doubles is that of their bit patterns
+      if (__ballot(best > best0) != 0) {
+        best = wave_max(best);
+        if (lane == 0)
+          atomicMax(best_bits, (unsigned long long)__double_as_longlong(best));
+      }
+    }
+  __syncthreads();
+}
+
+// The search of cell c by one workgroup; where too many nodes remain for it
+// (search_helpers, aux_kernels.h), only up to them: a.rest is for the helpers.
+template <int W>
+__device__ __forceinline__ void cell_search(const CellArgs& a, int c, float* sx) {
+  __shared__ double rv[W];
+  __shared__ int ri[W];
+  __shared__ float rb[W][6];
+  __shared__ unsigned long long best_bits;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ns = a.candidates[c];
+  float *sy = sx + a.cap, *sz = sy + a.cap;
+  float lo[3], hi[3];
+  load_candidates<W>(a, c, sx, lo, hi);
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
     const float l = wave_reduce(lo[d], Min()), h = wave_reduce(hi[d], Max());
@@ -609,98 +744,17 @@ __device__ __forceinline__ void cell_search(const CellArgs& a, int c, float* sx)
   // positive, or no number)
   const double gap = sqrt(L2) * (1.0 - 1e-12) - sqrt(R2) * (1.0 + 1e-12);
   const double least2 = gap > 0.0 ? gap * gap * (1.0 - 1e-12) : 0.0;
-  int kept = 0;
-  for (int b = 0; b < ns; b += 64 * W) {
-    const int k = b + tid;
-    float x = 0.f, yk = 0.f, z = 0.f;
-    bool keep = false;
-    if (k < ns) {
-      x = sx[k]; yk = sy[k]; z = sz[k];
-      keep = !(dist2(x - cx, yk - cy, z - cz) < least2);
-    }
-    const unsigned long long m = __ballot(keep);
-    if (lane == 0) ri[wave] = __popcll(m);
-    __syncthreads();  // (all positions of this round are in registers)
-    int at = kept;
-#pragma unroll
-    for (int w = 0; w < W; ++w) {
-      if (w < wave) at += ri[w];
-      kept += ri[w];
-    }
-    if (keep) {
-      at += __popcll(m & ((1ull << lane) - 1));
-      sx[at] = x; sy[at] = yk; sz[at] = z;
-    }
-    __syncthreads();  // ri is used again
-  }
-  // the last 64 are filled up with the last node, then the boxes
-  const int blocks = (kept + 63) / 64;
-  for (int b = wave; b < blocks; b += W) {
-    const int k = 64 * b + lane, from = min(k, kept - 1);
-    const float v[3] = {sx[from], sy[from], sz[from]};
-    wave_sync();
-    if (k >= kept) { sx[k] = v[0]; sy[k] = v[1]; sz[k] = v[2]; }
-    float* to = box + 6 * (k / kGroup);
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      const float lo = row_reduce(v[d], Min()), hi = row_reduce(v[d], Max());
-      if ((lane & 15) == 0) { to[d] = lo; to[3 + d] = hi; }
+  const int kept = keep_far_nodes<W>(a, ns, sx, cx, cy, cz, least2, ri);
+  if (a.helpers > 0) {
+    const bool leave = kept > max(kSearchNodes, ns / 8);
+    if (tid == 0)
+      a.rest[c] = SearchRest{{cx, cy, cz}, least2, leave ? 1 : 0};
+    if (leave) {
+      if (tid == 0) a.d2max[c] = (unsigned long long)__double_as_longlong(L2);
+      return;
     }
   }
-  if (tid == 0) best_bits = (unsigned long long)__double_as_longlong(L2);
-  __syncthreads();
-  // 64 rows (one a lane) against 64 column groups (one a lane for the test of
-  // boxes) at a time, round the wavefronts
-  double best = L2;  // per lane
-  const int groups = blocks * (64 / kGroup);
-  int turn = 0;
-  for (int g = 0; g < blocks; ++g)
-    for (int h0 = g * (64 / kGroup); h0 < groups; h0 += 64) {
-      const bool mine = turn == wave;
-      turn = turn + 1 == W ? 0 : turn + 1;
-      if (!mine) continue;
-      const double best0 = __longlong_as_double((long long)__hip_atomic_load(
-          &best_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
-      best = fmax(best, best0);
-      bool near = false;
-      if (h0 + lane < groups) {
-        const float* q = box + 6 * (h0 + lane);
-        const double q0 = q[0], q1 = q[1], q2 = q[2], q3 = q[3], q4 = q[4], q5 = q[5];
-#pragma unroll
-        for (int s = 0; s < 64 / kGroup; ++s) {
-          const float* r = box + 6 * (g * (64 / kGroup) + s);
-          const double ex = fmax(r[3] - q0, q3 - r[0]), ey = fmax(r[4] - q1, q4 - r[1]),
-                       ez = fmax(r[5] - q2, q5 - r[2]);
-          near |= !(dist2(ex, ey, ez) < best0 * (1.0 - 1e-12));
-        }
-      }
-      const double x = sx[64 * g + lane], yk = sy[64 * g + lane], z = sz[64 * g + lane];
-      for (unsigned long long todo = __ballot(near); todo != 0; todo &= todo - 1) {
-        const int h = h0 + __ffsll((long long)todo) - 1;
-        const float* q = box + 6 * h;
-        const double ex = fmax(x - q[0], q[3] - x), ey = fmax(yk - q[1], q[4] - yk),
-                     ez = fmax(z - q[2], q[5] - z);
-        if (__ballot(!(dist2(ex, ey, ez) < best * (1.0 - 1e-12))) == 0) continue;
-        const float4* vx = reinterpret_cast<const float4*>(sx + kGroup * h);
-        const float4* vy = reinterpret_cast<const float4*>(sy + kGroup * h);
-        const float4* vz = reinterpret_cast<const float4*>(sz + kGroup * h);
-#pragma unroll
-        for (int j = 0; j < kGroup / 4; ++j) {
-          const float4 u = vx[j], v = vy[j], w = vz[j];
-          best = fmax(best, dist2(x - u.x, yk - v.x, z - w.x));
-          best = fmax(best, dist2(x - u.y, yk - v.y, z - w.y));
-          best = fmax(best, dist2(x - u.z, yk - v.z, z - w.z));
-          best = fmax(best, dist2(x - u.w, yk - v.w, z - w.w));
-        }
-      }
-      // the maximum of non-negative doubles is that of their bit patterns
-      if (__ballot(best > best0) != 0) {
-        best = wave_max(best);
-        if (lane == 0)
-          atomicMax(&best_bits, (unsigned long long)__double_as_longlong(best));
-      }
-    }
-  __syncthreads();
+  search_pairs<W>(a, sx, kept, L2, 0, W, &best_bits);
   if (tid == 0) a.d2max[c] = best_bits;
 }
 
@@ -728,29 +782,71 @@ __global__ __launch_bounds__(64 * W) void shape_pass_kernel(CellArgs a) {
     tile_moments(a.mom, (int)t, lane, lds + (size_t)wave * a.mom.T.nloc);
 }
 
+// A helper of cell c: it loads the candidates again, keeps the same nodes and takes
+// its share of their pairs; the last of the cell's workgroups to arrive writes the
+// distance.
+constexpr int kFieldWaves = 4;
+
+__device__ __forceinline__ void help_search(const ShapeFinArgs& f, const CellArgs& a, int c,
+                                            int helper, float* sx) {
+  __shared__ int ri[kFieldWaves], flag;
+  __shared__ unsigned long long best_bits, start_bits;
+  const SearchRest r = a.rest[c];
+  if (r.left == 0) return;
+  const int tid = threadIdx.x;
+  if (tid == 0) start_bits = device_load(a.d2max + c);  // the others raise it
+  float lo[3], hi[3];
+  load_candidates<kFieldWaves>(a, c, sx, lo, hi);
+  __syncthreads();
+  const int kept = keep_far_nodes<kFieldWaves>(a, a.candidates[c], sx, r.centre[0], r.centre[1],
+                                               r.centre[2], r.least2, ri);
+  const unsigned long long start = start_bits;
+  search_pairs<kFieldWaves>(a, sx, kept, __longlong_as_double((long long)start),
+                            kFieldWaves * helper, kFieldWaves * a.helpers, &best_bits);
+  if (tid == 0 && best_bits > start) atomicMax(a.d2max + c, best_bits);
+  if (last_arrival(a.done + (int64_t)kDoneStride * c, a.helpers, tid, &flag) && tid == 0)
+    shape_distance(f, c, __longlong_as_double((long long)device_load(a.d2max + c)));
+}
+
 // The cell's fields, by one wavefront; all four search all node pairs first if
 // the cell has a tetrahedron that is not positively oriented, which the
-// candidates do not cover.
-__global__ __launch_bounds__(256) void shape_cell_kernel(ShapeFinArgs f,
-                                                         const int32_t* tile_inv) {
-  __shared__ double rv[4];
+// candidates do not cover.  HELP: behind the cells' workgroups, the helpers of
+// each.
+template <bool HELP>
+__global__ __launch_bounds__(64 * kFieldWaves) void shape_cell_kernel(ShapeFinArgs f,
+                                                                      const int32_t* tile_inv,
+                                                                      CellArgs a) {
+  extern __shared__ float4 lds[];
+  __shared__ double rv[kFieldWaves];
+  __shared__ int flag;
   const int c = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
-  int inv = 0;
-  {
-    const int t0 = f.T.cell_tile_first[c], nt = f.T.cell_tile_count[c];
-    for (int k = tid; k < nt; k += 256)
-      inv |= tile_inv[t0 + (int64_t)k * f.T.tile_stride];
+  if (!HELP || c < f.T.n_cells) {
+    int inv = 0;
+    {
+      const int t0 = f.T.cell_tile_first[c], nt = f.T.cell_tile_count[c];
+      for (int k = tid; k < nt; k += 64 * kFieldWaves)
+        inv |= tile_inv[t0 + (int64_t)k * f.T.tile_stride];
+    }
+    const bool left = HELP && a.rest[c].left != 0;
+    double d2 = left ? 0.0 : __longlong_as_double((long long)f.d2max[c]);
+    if (__syncthreads_or(inv != 0)) {
+      const double m = wave_max(all_pairs(f.y, f.T.n_nodes, f.node_off[c], f.node_off[c + 1]));
+      if (lane == 0) rv[tid >> 6] = m;
+      __syncthreads();
+      d2 = fmax(fmax(d2, fmax(rv[0], rv[1])), fmax(rv[2], rv[3]));
+    }
+    if (tid < 64) shape_fields(f, c, lane);
+    if (left) {
+      if (tid == 0 && d2 > 0.0)
+        atomicMax(a.d2max + c, (unsigned long long)__double_as_longlong(d2));
+      if (!last_arrival(a.done + (int64_t)kDoneStride * c, a.helpers, tid, &flag)) return;
+      d2 = __longlong_as_double((long long)device_load(a.d2max + c));
+    }
+    if (tid == 0) shape_distance(f, c, d2);
+    return;
   }
-  double d2 = __longlong_as_double((long long)f.d2max[c]);
-  if (__syncthreads_or(inv != 0)) {
-    const double m = wave_max(all_pairs(f.y, f.T.n_nodes, f.node_off[c], f.node_off[c + 1]));
-    if (lane == 0) rv[tid >> 6] = m;
-    __syncthreads();
-    d2 = fmax(fmax(d2, fmax(rv[0], rv[1])), fmax(rv[2], rv[3]));
-  }
-  if (tid >= 64) return;
-  shape_fields(f, c, lane);
-  if (lane == 0) shape_distance(f, c, d2);
+  if constexpr (HELP)
+    help_search(f, a, c % f.T.n_cells, c / f.T.n_cells - 1, reinterpret_cast<float*>(lds));
 }
 
 }  // namespace
@@ -780,7 +876,7 @@ hipError_t launch_shape(const DeviceTables& T, const int64_t* node_off,
   const size_t mom_lds = per * shape_lds(T.nloc);
   const ShapeFinArgs f{T, node_off, y, S.mom, S.d2max, d_ref, out};
   if (S.cell_nodes > 0) {
-    const CellArgs a{m, S.order, S.candidates, S.d2max, S.cell_nodes};
+    const CellArgs a{m, S.order, S.candidates, S.d2max, S.cell_nodes, S.helpers, S.rest, S.done};
     const size_t lds = std::max(mom_lds, cell_lds(S.cell_nodes));
     if (waves == 4)
       hipLaunchKernelGGL(shape_pass_kernel<4>, dim3(nc + mom_blocks), dim3(256), lds, st, a);
@@ -788,8 +884,13 @@ hipError_t launch_shape(const DeviceTables& T, const int64_t* node_off,
       hipLaunchKernelGGL(shape_pass_kernel<kMomWaves>, dim3(nc + mom_blocks),
                          dim3(64 * kMomWaves), lds, st, a);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(shape_cell_kernel, dim3(nc), dim3(256), 0, st, f,
-                       (const int32_t*)S.tile_inv);
+    if (S.helpers > 0)
+      hipLaunchKernelGGL(shape_cell_kernel<true>, dim3((unsigned)nc * (1 + S.helpers)),
+                         dim3(64 * kFieldWaves), cell_lds(S.cell_nodes), st, f,
+                         (const int32_t*)S.tile_inv, a);
+    else
+      hipLaunchKernelGGL(shape_cell_kernel<false>, dim3(nc), dim3(64 * kFieldWaves), 0, st, f,
+                         (const int32_t*)S.tile_inv, a);
     return hipGetLastError();
   }
   if (mom_blocks > 0) {

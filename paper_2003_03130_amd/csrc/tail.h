@@ -28,17 +28,6 @@ namespace cm {
 // the search direction) to their conjugate-gradient iteration.
 enum Tail { kNoTail, kCellSums, kCgPlates, kCgSphere };
 
-// Whether this workgroup's tile is the last of cell c to arrive, uniform over the
-// workgroup.  flag: an int of LDS that the tile no longer uses.
-__device__ __forceinline__ bool last_of_cell(uint32_t* done, int c, uint32_t last, int tid,
-                                             int* flag) {
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __syncthreads();
-  if (tid == 0) *flag = atomicInc(done + (int64_t)kDoneStride * c, last) == last;
-  __syncthreads();
-  return *flag != 0;
-}
-
 template <int L, bool FWD, bool BWD, bool PL, bool GRAD>
 __device__ __forceinline__ void cell_tail(const WideArgs& a, int c, int tid, int* flag) {
   constexpr int W = L / 64;
@@ -50,7 +39,7 @@ __device__ __forceinline__ void cell_tail(const WideArgs& a, int c, int tid, int
   // the slots of the thread's first node, while the stores are on their way
   SharedSlots sl{};
   if (s0 + tid < s1) sl = shared_slots(a.T.shared_rec[s0 + tid], a.T.shared_rec4);
-  if (!last_of_cell(a.out.done, c, last, tid, flag)) return;
+  if (!last_arrival(a.out.done + (int64_t)kDoneStride * c, last, tid, flag)) return;
 
   float top = 0.f, bot = 0.f, gw = 0.f;
   if constexpr (PL) {
@@ -143,7 +132,7 @@ __device__ __forceinline__ void cg_tail(const WideArgs& a, int c, int tid, int* 
   const int64_t n0 = g.node_off[c], n1 = g.node_off[c + 1];
   const double top = g.plate[2 * c], bot = g.plate[2 * c + 1];
   const ShrRange sr = shared_range(g, c, n1);
-  if (!last_of_cell(a.out.done, c, last, tid, flag)) return;
+  if (!last_arrival(a.out.done + (int64_t)kDoneStride * c, last, tid, flag)) return;
   cg_step_regs<2, SPH, true>(g, g.st + kQsState * c, c, n0, n1, top, bot, red, sr);
 }
 
