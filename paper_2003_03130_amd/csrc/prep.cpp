@@ -9,13 +9,30 @@
 #include <atomic>
 #include <cmath>
 #include <cstring>
+#include <new>
 #include <numeric>
+#include <system_error>
 #include <thread>
 
 #include "cellmech.h"
 
 namespace cm {
 namespace {
+
+// work() on this thread and on up to n - 1 further ones: as many as the system
+// starts (an exception must not pass a running thread, nor the C entry above).
+// work may not throw.
+template <class F>
+void on_threads(int64_t n, const F& work) {
+  std::vector<std::thread> pool;
+  try {
+    for (int64_t i = 1; i < n; ++i) pool.emplace_back(work);
+  } catch (const std::system_error&) {
+  } catch (const std::bad_alloc&) {
+  }
+  work();
+  for (auto& th : pool) th.join();
+}
 
 struct CellOut {
   int status = CM_OK;
@@ -699,19 +716,20 @@ int prepare_batch(int32_t n_cells, const int64_t* node_off,
     for (;;) {
       int32_t c = next_cell.fetch_add(1);
       if (c >= n_cells) break;
-      prepare_cell(c, node_off[c + 1] - node_off[c], tet_off[c + 1] - tet_off[c],
-                   ref_xyz + 3 * node_off[c], tets + 4 * tet_off[c],
-                   tet_region ? tet_region + tet_off[c] : nullptr, n_regions, opt,
-                   cells[c]);
+      try {
+        prepare_cell(c, node_off[c + 1] - node_off[c], tet_off[c + 1] - tet_off[c],
+                     ref_xyz + 3 * node_off[c], tets + 4 * tet_off[c],
+                     tet_region ? tet_region + tet_off[c] : nullptr, n_regions, opt,
+                     cells[c]);
+      } catch (const std::bad_alloc&) {
+        cells[c].status = CM_ENOMEM;
+      }
     }
   };
-  std::vector<std::thread> pool;
-  for (unsigned i = 1; i < nt; ++i) pool.emplace_back(work);
-  work();
-  for (auto& th : pool) th.join();
+  on_threads(nt, work);
   for (auto& cell : cells)
     if (cell.status != CM_OK) {
-      *err = cell.err;
+      *err = cell.status == CM_ENOMEM ? "host allocation failed" : cell.err;
       return cell.status;
     }
 
@@ -893,7 +911,7 @@ int prepare_template(int32_t n_cells, int64_t n_nodes, int64_t n_tets,
   return CM_OK;
 }
 
-bool list_tables(const Prepared& P, ListHost* out) {
+bool list_tables(const Prepared& P, ListHost* out) try {
   const int64_t n_tiles = (int64_t)P.tiles.size();
   // a shared mesh has every tile n_cells times in a row, with one chunk range
   const int64_t copies = P.tile_stride;
@@ -956,15 +974,17 @@ bool list_tables(const Prepared& P, ListHost* out) {
   std::atomic<int64_t> next_block(0);
   std::atomic<bool> fits(true);
   auto work = [&]() {
-    for (int64_t b; (b = next_block.fetch_add(1)) < n_blocks;)
-      if (!tile_block(b * copies, block[b])) fits = false;
+    for (int64_t b; (b = next_block.fetch_add(1)) < n_blocks;) {
+      try {
+        if (!tile_block(b * copies, block[b])) fits = false;
+      } catch (const std::bad_alloc&) {
+        fits = false;
+      }
+    }
   };
-  const int64_t nt = std::min<int64_t>(
-      std::max(1u, std::min(16u, std::thread::hardware_concurrency())), n_blocks / 8);
-  std::vector<std::thread> pool;
-  for (int64_t i = 1; i < nt; ++i) pool.emplace_back(work);
-  work();
-  for (auto& th : pool) th.join();
+  on_threads(std::min<int64_t>(
+                 std::max(1u, std::min(16u, std::thread::hardware_concurrency())), n_blocks / 8),
+             work);
   if (!fits) return false;
   for (const auto& o : block)
     out->stride16 = std::max(out->stride16, (int32_t)(o.size() / 8));
@@ -973,6 +993,8 @@ bool list_tables(const Prepared& P, ListHost* out) {
     std::copy(block[b].begin(), block[b].end(),
               out->blocks.begin() + b * (size_t)out->stride16 * 8);
   return true;
+} catch (const std::bad_alloc&) {
+  return false;
 }
 
 }  // namespace cm

@@ -81,7 +81,7 @@ int prepare_batch(int32_t n_cells, const int64_t* node_off,
 //            chunk << 8 | lane << 2 | vertex slot, or chunks << 8 (a
 //            contribution of zero) where a node has no more.
 // The copies of a shared mesh share the blocks.  False where the 16-bit
-// numbers do not reach.
+// numbers do not reach, or the host's memory.
 constexpr uint16_t kNoNode = 0xffff;
 struct ListHost {
   std::vector<uint16_t> blocks;
