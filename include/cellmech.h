@@ -379,9 +379,9 @@ int cm_autotune(cm_batch h, const float* y, const char* cache_path,
  *   mode 6: forward and backward in one pass (cm_forces_and_backward).
  * Pointers are captured as given and must stay valid while the graph is
  * used.  Re-capturing replaces the previous graph.  cm_graph_launch replays
- * it on `stream` (CM_ESTATE if nothing was captured); modes 0, 1 and 6, two
- * or four kernels, are replayed as these launches, which costs the host less
- * than launching a graph.
+ * it on `stream` (CM_ESTATE if nothing was captured); modes 0, 1 and 6, one
+ * or two kernels a pass, are replayed as these launches, which costs the host
+ * less than launching a graph.
  */
 int cm_graph_capture(cm_batch h, int mode, const float* y, float* f,
                      double* energy, int32_t* n_inverted, const float* fbar,
@@ -673,6 +673,9 @@ int cm_shape(cm_batch h, const float* y, const double* d_ref, double* out,
  *   ms[4] tile kernel and ms[5] finalize kernel of cm_forces_and_backward
  *         (NaN where that pass does not apply: aliased buffers or too
  *         little LDS).
+ * The finalize entry is 0 for a pass whose tile kernel forms the cells' sums
+ * itself (batches of up to 256 tiles at the default launch, depending on the
+ * cells' shared nodes): it launches no other.
  * Buffers as in cm_forces / cm_forces_backward (fbar, ebar nullable);
  * ms holds 6 entries.
  * Synchronises the stream; not graph-safe.

@@ -410,7 +410,8 @@ class CellBatch:
                         reps=10, stream=None):
         """Average ms per launch of the forward tile, forward finalize,
         backward tile and backward finalize kernels and of the fused forward
-        + backward tile and finalize kernels (HIP events)."""
+        + backward tile and finalize kernels (HIP events); 0 for a finalize
+        that the pass does not launch."""
         ms = np.zeros(6, dtype=np.float64)
         nat.check(nat.lib().cm_profile_kernels(
             self._h, _ptr(y), _ptr(f), _ptr(energy), _ptr(fbar), _ptr(ebar),

@@ -1299,6 +1299,16 @@ int cm_profile_kernels(cm_batch h, const float* y, float* f, double* energy,
   cm::LaunchCfg fcfg;
   const bool fused = fused_cfg(h, &fcfg) && f != ybar && f != y && ybar != y &&
                      (!fbar || (f != fbar && ybar != fbar));
+  // the route that an evaluation takes: where the tile kernel forms the cells'
+  // sums itself there is no finalize launch
+  const bool grad = ebar != nullptr || thetabar != nullptr;
+  const bool tail[3] = {cm::use_tail(h->T, r, h->cfg, true, false, false),
+                        cm::use_tail(h->Tb, r, h->cfg, false, true, grad),
+                        fused && cm::use_tail(h->T, r, fcfg, true, true, grad)};
+  const cm::CellOut out[3] = {
+      {tail[0] ? h->T.cell_done : nullptr, energy, nullptr, nullptr, nullptr},
+      {tail[1] ? h->Tb.cell_done : nullptr, nullptr, nullptr, nullptr, thetabar},
+      {tail[2] ? h->T.cell_done : nullptr, energy, nullptr, nullptr, thetabar}};
   hipEvent_t ev[7];
   for (int i = 0; i < 7; ++i) CM_HIP(hipEventCreate(&ev[i]));
   int rc = CM_OK;
@@ -1307,15 +1317,23 @@ int cm_profile_kernels(cm_batch h, const float* y, float* f, double* energy,
       ms[k] = NAN;
       continue;
     }
+    if (k % 2 == 1 && tail[k / 2]) {
+      ms[k] = 0.0;
+      continue;
+    }
     auto once = [&]() -> hipError_t {
       switch (k) {
-        case 0: return cm::launch_forward_main(h->T, r, h->cfg, y, f, st);
+        case 0:
+          return cm::launch_forward_main(h->T, r, h->cfg, y, f, st, cm::PlateFwd{}, false,
+                                         out[0]);
         case 1: return cm::launch_forward_finalize(h->T, r, f, energy, nullptr, st);
-        case 2: return cm::launch_backward_main(h->Tb, r, h->cfg, y, fbar, ebar, ybar, st);
+        case 2:
+          return cm::launch_backward_main(h->Tb, r, h->cfg, y, fbar, ebar, ybar, st,
+                                          cm::CellMask{}, cm::PlateBwd{}, grad, out[1]);
         case 3: return cm::launch_backward_finalize(h->Tb, r, ybar, thetabar, st);
         case 4:
           return cm::launch_forward_backward_main(h->T, h->Tb, r, fcfg, y, f, fbar, ebar,
-                                                  ybar, st);
+                                                  ybar, st, grad, out[2]);
         default:
           return cm::launch_forward_backward_finalize(h->T, h->Tb, r, f, energy, nullptr,
                                                       ybar, thetabar, st);
@@ -1382,10 +1400,11 @@ int cm_graph_capture(cm_batch h, int mode, const float* y, float* f,
   }
   if (e != hipSuccess) return fail(CM_EHIP, std::string("hipStreamEndCapture: ") + hipGetErrorString(e));
   if (!percell && !fork) {
-    // Two launches (four in mode 1): issued one by one they cost the host less
-    // than a graph launch (9 against 19 us with the call, 15 against 22 in mode
-    // 1; 110k tets: 20.7 -> 12.7, 24.2 -> 20.2 us a replay), and take the same
-    // arguments, so the graph was only captured to have them checked.
+    // One or two launches a pass (mode 1: two passes): issued one by one they cost
+    // the host less than a graph launch (9 against 19 us for two with the call, 15
+    // against 22 for four; 110k tets: 20.7 -> 12.7, mode 1 24.2 -> 20.2 us a
+    // replay), and take the same arguments, so the graph was only captured to have
+    // them checked.
     (void)hipGraphDestroy(g);
     cm::LaunchCfg cfg = h->cfg;
     if (fused) (void)fused_cfg(h, &cfg);

@@ -50,7 +50,7 @@ struct cm_batch_s {
   bool is_template = false;  // cells share one chunk array (tiles interleaved)
   cm::Indenter qs_ind;       // top contact of the quasi-static entry points
   // captured evaluation (cm_graph_capture): a graph, or the arguments of one
-  // that is two or four launches (mode >= 0)
+  // that is one or two launches a pass (mode >= 0)
   hipGraph_t graph = nullptr;
   hipGraphExec_t graph_exec = nullptr;
   struct Replay {
