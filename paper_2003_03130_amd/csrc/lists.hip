@@ -261,13 +261,15 @@ bool use_lists(const DeviceTables& T, const Range& r, const LaunchCfg& cfg, bool
          list_lds(T.nloc, T.lists, fwd, bwd, grad) <= 163840;
 }
 
-// Most shared nodes of a cell for whose sums one workgroup is faster than a
-// finalize launch, finalize -> tail: single passes at 1,512 shared nodes 11.1,
-// 11.4, 11.3 -> 8.9, 10.6, 9.4 us (forward, adjoint, Hessian-vector product), at
-// 2,607 11.0, 11.3, 10.8 -> 10.4, 12.1, 11.4, at 4,820 10.8 -> 14.6; both passes
-// at 331 12.5 -> 11.8, at 1,040 12.0 -> 12.6.  Passes with more than 256 tiles
-// keep the finalize: several workgroups share a CU there, and the arrival of a
-// tile's stores holds up the next tile (forward of 650 tiles 13.9 -> 18.4).
+// Most shared nodes of a cell whose sums one workgroup forms in place of a finalize
+// launch, finalize -> tail: at 1,512 all single passes are faster, 11.1, 11.4, 11.3
+// -> 8.9, 10.6, 9.4 us (forward, adjoint, Hessian-vector product); at 2,607 the
+// adjoint and the product are slower, 11.3, 10.8 -> 12.1, 11.4; the forward, which
+// has the same limit, still gains there, 11.0 -> 10.4, and loses at 4,820, 10.8 ->
+// 14.6.  Both passes at once gain at 331, 12.5 -> 11.8, and lose at 1,040, 12.0 ->
+// 12.6; nothing was measured between.  Passes with more than 256 tiles keep the
+// finalize: several workgroups share a CU there, and the arrival of a tile's
+// stores holds up the next tile (forward of 650 tiles 13.9 -> 18.4).
 constexpr int kTailShared = 2048, kTailSharedBoth = 512;
 
 bool use_tail(const DeviceTables& T, const Range& r, const LaunchCfg& cfg, bool fwd, bool bwd,
