@@ -61,24 +61,29 @@ F_TOL, E_TOL, G_TOL = 1e-5, 1e-6, 1e-5
 TILE_KERNEL_SOURCES = ("kernels.hip", "backward.hip", "fused.hip", "wide.hip",
                        "wide.h", "lists.hip", "tail.h", "cg.h", "device_util.h",
                        "finalize.h", "kernels.h", "layout.h", "mr_tet.h",
-                       "prep.cpp", "util.hip")
+                       "plate.h", "aux_kernels.h", "prep.cpp", "prep.h",
+                       "util.hip")
 
 
-def kernel_source_hash():
+def kernel_source_hash(csrc=os.path.join(ROOT, "paper_2003_03130_amd", "csrc")):
     """sha256 of the sources of the forward and backward kernels (their .hip
     files and the headers they include) and of the host code that lays out
     their data (prep.cpp: tiles, slots, chunks), and of the reference copy
-    kernel the counters are scaled by (util.hip); a stored counter record
-    applies only to the kernels and layout it was measured on.  The other
-    host code and the auxiliary kernels (plates, quasi-static, shape) are
-    not part of it."""
+    kernel the counters are scaled by (util.hip), without their comments and
+    blank lines; a stored counter record applies only to the kernels and
+    layout it was measured on.  The other host code and the auxiliary kernels
+    (plates, quasi-static, shape) are not part of it."""
     import hashlib
+    import re
     h = hashlib.sha256()
-    csrc = os.path.join(ROOT, "paper_2003_03130_amd", "csrc")
-    for fn in sorted(os.listdir(csrc)):
-        if fn in TILE_KERNEL_SOURCES:
-            with open(os.path.join(csrc, fn), "rb") as fh:
-                h.update(fn.encode() + fh.read())
+    for fn in sorted(TILE_KERNEL_SOURCES):
+        with open(os.path.join(csrc, fn), encoding="utf-8") as fh:
+            text = fh.read()
+        # comments, but not what looks like one inside a string
+        text = re.sub(r'("(?:\\.|[^"\\\n])*")|//[^\n]*|/\*.*?\*/',
+                      lambda m: m.group(1) or " ", text, flags=re.S)
+        lines = [" ".join(line.split()) for line in text.splitlines()]
+        h.update((fn + "\n" + "\n".join(x for x in lines if x)).encode())
     return h.hexdigest()
 
 
