@@ -1,15 +1,15 @@
 // Device data layout of a prepared batch of tetrahedral cells.
 //
-// Tetrahedra are grouped into tiles of at most `tile_tets` tetrahedra, one
-// wavefront (64 lanes) per tile, processed 64 at a time ("chunks").  A tile's distinct vertices ("tile nodes")
-// are staged in LDS; the tile's tetrahedra refer to them by 16-bit local
-// index.  Nodes touched by exactly one tile are "owned" and numbered so that
+// Tetrahedra are grouped into tiles of at most `tile_tets` tetrahedra, each
+// evaluated by one workgroup or wavefront, 64 tetrahedra ("chunks", one per
+// lane) at a time.  A tile's distinct vertices ("tile nodes") are staged in LDS;
+// the tile's tetrahedra refer to them by 16-bit local index.  Nodes touched by exactly one tile are "owned" and numbered so that
 // each tile's owned nodes form one contiguous internal range: the tile loads
 // their positions and stores their forces with plain coalesced accesses.
 // Nodes touched by several tiles are "shared": every (tile, shared node) pair
-// is a "slot"; the tile writes its partial force to the slot, and a second
-// pass sums the slots of each shared node in tile order.  No atomics are used
-// anywhere and the result is deterministic.
+// is a "slot"; the tile writes its partial force to the slot, and a second pass,
+// or the workgroup of the cell's last tile, sums the slots of each shared node in
+// tile order.  No value is added by an atomic, and the result is deterministic.
 #pragma once
 #include <cstdint>
 
