@@ -134,10 +134,10 @@ static int create_from(cm::Prepared& P, const cm::PrepOptions& po,
   // stream synchronisation below
   std::vector<int32_t> shared_cell, orphan_off, orphan, slot_first, shared_first;
   std::vector<int4> pc, rec, rec4;
-  std::vector<int32_t> more, cand;
-  std::vector<uint32_t> done, searched;
+  std::vector<int32_t> more, cand, helpers;
+  std::vector<uint32_t> done;
   cm::ListHost lists;
-  std::vector<int2> nbk;
+  std::vector<int2> nbk, helper;
   {
     cm::TileDesc* tiles;
     cm::TetChunk* chunks;
@@ -262,7 +262,7 @@ static int create_from(cm::Prepared& P, const cm::PrepOptions& po,
     cm::ShapeTables& S = h->shape;
     if (most_cand <= cm::kCellNodes) {
       S.cell_nodes = (most_cand + 63) & ~63;
-      S.helpers = cm::search_helpers(h->n_cells, most_cand);
+      cm::search_helpers(cand, &helpers, &helper);
     } else {
       // 256 x 256 node-pair blocks of every cell (row block <= column block);
       // the cell's nodes are ordered candidates first, so the pairs of the
@@ -291,11 +291,16 @@ static int create_from(cm::Prepared& P, const cm::PrepOptions& po,
         (rc = h->alloc(&S.cell_inv, (size_t)h->n_cells)) ||
         (rc = h->alloc(&S.d2max, (size_t)h->n_cells)))
       return bail(rc);
-    if (S.helpers > 0) {
-      searched.assign(h->n_cells * cm::kDoneStride, 0);
+    if (!helper.empty()) {
+      int32_t* dhelpers;
+      int2* dhelper;
       if ((rc = h->alloc(&S.rest, (size_t)h->n_cells)) ||
-          (rc = h->upload(&S.done, searched, stream)))
+          (rc = h->upload(&dhelpers, helpers, stream)) ||
+          (rc = h->upload(&dhelper, helper, stream)))
         return bail(rc);
+      S.helpers = dhelpers;
+      S.helper = dhelper;
+      S.n_helpers = (int32_t)helper.size();
     }
     S.cand_blocks = pcd;
     S.n_cand_blocks = (int64_t)pc.size();

@@ -6,6 +6,7 @@
 
 #include <algorithm>
 #include <cstdint>
+#include <vector>
 
 #include "kernels.h"
 
@@ -20,9 +21,10 @@ constexpr int kShapeFields = 10;
 constexpr int kCellNodes = 4096;
 // The workgroup that searches a cell compares alone the pairs of up to kSearchNodes
 // remaining nodes, or of an eighth of the candidates if that is more; those of more
-// (near-spherical cells, where all remain) it leaves to `helpers` further workgroups
-// of shape_cell_kernel.  0: none, each takes all of its cell, in handles
-// without such cells and beyond 256 cells, whose searches fill the chip.
+// (near-spherical cells, where all remain) it leaves to helpers, up to 32 further
+// workgroups of the cell: of 1,024 its share by the square of its candidates, none
+// if that is below four (many cells of one size, whose searches fill the chip, and
+// the small ones beside large ones).
 // Equal spheres, alone -> with helpers, and by the block search: 1 cell of 2,000
 // nodes 47 -> 22 us (46), of 9,000 185 -> 41 (54), of 20,000 334 -> 64 (68); 64 cells
 // of 2,000 48 -> 25 (58), of 20,000 343 -> 158 (222); 256 of 9,000 197 -> 173 (259).
@@ -31,14 +33,30 @@ constexpr int kCellNodes = 4096;
 // shared; but with 293 of 3,670 candidates left, which every helper loads again, 64
 // cells of 20,000 nodes 41 alone, 60 shared.
 constexpr int kSearchNodes = 256;
-inline int search_helpers(int64_t n_cells, int most_candidates) {
-  if (most_candidates <= kSearchNodes || most_candidates > kCellNodes || n_cells > 256) return 0;
-  return (int)std::min<int64_t>(32, 1024 / n_cells);
+// Helpers of every cell and, a pair for each of them, the cell and the helper's
+// number.
+inline void search_helpers(const std::vector<int32_t>& candidates,
+                           std::vector<int32_t>* helpers, std::vector<int2>* list) {
+  double all = 0.0;
+  for (int32_t n : candidates) all += (double)n * n;
+  helpers->assign(candidates.size(), 0);
+  for (size_t c = 0; c < candidates.size(); ++c) {
+    const double n = candidates[c];
+    const int share = (int)std::min(32.0, 1024.0 * n * n / all);
+    if (candidates[c] <= kSearchNodes || share < 4) continue;
+    (*helpers)[c] = share;
+  }
+  // one of each cell after the other: those of a cell are then mostly on one XCD,
+  // whose L2 has its candidates (64 cells of 2,000 nodes 39 -> 25 us)
+  for (int i = 0; i < 32; ++i)
+    for (size_t c = 0; c < candidates.size(); ++c)
+      if (i < (*helpers)[c]) list->push_back(make_int2((int)c, i));
 }
 // What such a search leaves: the nodes at least sqrt(least2) from the centre.
-struct SearchRest {
+struct alignas(64) SearchRest {
   double centre[3], least2;
-  int32_t left;  // whether it left any
+  int32_t left;   // to how many helpers (0: the search is done)
+  uint32_t done;  // workgroups of the cell that have arrived
 };
 // Tables and scratch of a handle's shape diagnostics.  cell_nodes: the
 // room of the search of one workgroup per cell, or 0 where some cell has more
@@ -61,10 +79,10 @@ struct ShapeTables {
   int32_t* cell_inv = nullptr;          // per cell (block search)
   double* bbox = nullptr;
   unsigned long long* d2max = nullptr;  // per cell
-  int32_t helpers = 0;                  // search_helpers of the handle
-  SearchRest* rest = nullptr;           // per cell (helpers > 0)
-  uint32_t* done = nullptr;             // per cell, kDoneStride apart: workgroups
-                                        // of the cell that have arrived
+  const int32_t* helpers = nullptr;     // search_helpers of the handle
+  const int2* helper = nullptr;
+  int32_t n_helpers = 0;
+  SearchRest* rest = nullptr;           // per cell (with helpers)
 };
 size_t shape_lds(int nloc);
 hipError_t launch_shape(const DeviceTables& T, const int64_t* node_off,

@@ -500,9 +500,9 @@ struct CellArgs {
   const int32_t* candidates;  // per cell: how many of them are candidates
   unsigned long long* d2max;
   int32_t cap;                // nodes that the LDS holds (multiple of 64)
-  int32_t helpers;            // as in ShapeTables, with rest and done
-  SearchRest* rest;
-  uint32_t* done;
+  const int32_t* helpers;     // these as in ShapeTables
+  const int2* helper;
+  SearchRest* rest;           // null: no helpers
 };
 
 // Largest value over the workgroup (v >= 0) on every thread, and one of the
@@ -745,10 +745,10 @@ __device__ __forceinline__ void cell_search(const CellArgs& a, int c, float* sx)
   const double gap = sqrt(L2) * (1.0 - 1e-12) - sqrt(R2) * (1.0 + 1e-12);
   const double least2 = gap > 0.0 ? gap * gap * (1.0 - 1e-12) : 0.0;
   const int kept = keep_far_nodes<W>(a, ns, sx, cx, cy, cz, least2, ri);
-  if (a.helpers > 0) {
-    const bool leave = kept > max(kSearchNodes, ns / 8);
-    if (tid == 0)
-      a.rest[c] = SearchRest{{cx, cy, cz}, least2, leave ? 1 : 0};
+  if (a.rest) {
+    const int helpers = a.helpers[c];
+    const bool leave = helpers > 0 && kept > max(kSearchNodes, ns / 8);
+    if (tid == 0) a.rest[c] = SearchRest{{cx, cy, cz}, least2, leave ? helpers : 0, 0};
     if (leave) {
       if (tid == 0) a.d2max[c] = (unsigned long long)__double_as_longlong(L2);
       return;
@@ -783,15 +783,16 @@ __global__ __launch_bounds__(64 * W) void shape_pass_kernel(CellArgs a) {
 }
 
 // A helper of cell c: it loads the candidates again, keeps the same nodes and takes
-// its share of their pairs; the last of the cell's workgroups to arrive writes the
-// distance.
+// its share of their pairs; with LAST, the last of the cell's workgroups to arrive
+// writes the distance.
 constexpr int kFieldWaves = 4;
 
+template <bool LAST>
 __device__ __forceinline__ void help_search(const ShapeFinArgs& f, const CellArgs& a, int c,
                                             int helper, float* sx) {
   __shared__ int ri[kFieldWaves], flag;
   __shared__ unsigned long long best_bits, start_bits;
-  const SearchRest r = a.rest[c];
+  const SearchRest r = a.rest[c];  // (but its counter)
   if (r.left == 0) return;
   const int tid = threadIdx.x;
   if (tid == 0) start_bits = device_load(a.d2max + c);  // the others raise it
@@ -802,10 +803,20 @@ __device__ __forceinline__ void help_search(const ShapeFinArgs& f, const CellArg
                                                r.centre[2], r.least2, ri);
   const unsigned long long start = start_bits;
   search_pairs<kFieldWaves>(a, sx, kept, __longlong_as_double((long long)start),
-                            kFieldWaves * helper, kFieldWaves * a.helpers, &best_bits);
+                            kFieldWaves * helper, kFieldWaves * r.left, &best_bits);
   if (tid == 0 && best_bits > start) atomicMax(a.d2max + c, best_bits);
-  if (last_arrival(a.done + (int64_t)kDoneStride * c, a.helpers, tid, &flag) && tid == 0)
-    shape_distance(f, c, __longlong_as_double((long long)device_load(a.d2max + c)));
+  if constexpr (LAST) {
+    if (last_arrival(&a.rest[c].done, r.left, tid, &flag) && tid == 0)
+      shape_distance(f, c, __longlong_as_double((long long)device_load(a.d2max + c)));
+  }
+}
+
+// The helpers in a launch of their own.
+__global__ __launch_bounds__(64 * kFieldWaves) void shape_help_kernel(ShapeFinArgs f,
+                                                                      CellArgs a) {
+  extern __shared__ float4 lds[];
+  const int2 w = a.helper[blockIdx.x];
+  help_search<false>(f, a, w.x, w.y, reinterpret_cast<float*>(lds));
 }
 
 // The cell's fields, by one wavefront; all four search all node pairs first if
@@ -827,7 +838,7 @@ __global__ __launch_bounds__(64 * kFieldWaves) void shape_cell_kernel(ShapeFinAr
       for (int k = tid; k < nt; k += 64 * kFieldWaves)
         inv |= tile_inv[t0 + (int64_t)k * f.T.tile_stride];
     }
-    const bool left = HELP && a.rest[c].left != 0;
+    const int left = HELP ? a.rest[c].left : 0;
     double d2 = left ? 0.0 : __longlong_as_double((long long)f.d2max[c]);
     if (__syncthreads_or(inv != 0)) {
       const double m = wave_max(all_pairs(f.y, f.T.n_nodes, f.node_off[c], f.node_off[c + 1]));
@@ -839,14 +850,16 @@ __global__ __launch_bounds__(64 * kFieldWaves) void shape_cell_kernel(ShapeFinAr
     if (left) {
       if (tid == 0 && d2 > 0.0)
         atomicMax(a.d2max + c, (unsigned long long)__double_as_longlong(d2));
-      if (!last_arrival(a.done + (int64_t)kDoneStride * c, a.helpers, tid, &flag)) return;
+      if (!last_arrival(&a.rest[c].done, left, tid, &flag)) return;
       d2 = __longlong_as_double((long long)device_load(a.d2max + c));
     }
     if (tid == 0) shape_distance(f, c, d2);
     return;
   }
-  if constexpr (HELP)
-    help_search(f, a, c % f.T.n_cells, c / f.T.n_cells - 1, reinterpret_cast<float*>(lds));
+  if constexpr (HELP) {
+    const int2 w = a.helper[c - f.T.n_cells];
+    help_search<true>(f, a, w.x, w.y, reinterpret_cast<float*>(lds));
+  }
 }
 
 }  // namespace
@@ -876,7 +889,8 @@ hipError_t launch_shape(const DeviceTables& T, const int64_t* node_off,
   const size_t mom_lds = per * shape_lds(T.nloc);
   const ShapeFinArgs f{T, node_off, y, S.mom, S.d2max, d_ref, out};
   if (S.cell_nodes > 0) {
-    const CellArgs a{m, S.order, S.candidates, S.d2max, S.cell_nodes, S.helpers, S.rest, S.done};
+    const CellArgs a{m, S.order, S.candidates, S.d2max, S.cell_nodes, S.helpers,
+                     S.helper, S.rest};
     const size_t lds = std::max(mom_lds, cell_lds(S.cell_nodes));
     if (waves == 4)
       hipLaunchKernelGGL(shape_pass_kernel<4>, dim3(nc + mom_blocks), dim3(256), lds, st, a);
@@ -884,13 +898,22 @@ hipError_t launch_shape(const DeviceTables& T, const int64_t* node_off,
       hipLaunchKernelGGL(shape_pass_kernel<kMomWaves>, dim3(nc + mom_blocks),
                          dim3(64 * kMomWaves), lds, st, a);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    if (S.helpers > 0)
-      hipLaunchKernelGGL(shape_cell_kernel<true>, dim3((unsigned)nc * (1 + S.helpers)),
-                         dim3(64 * kFieldWaves), cell_lds(S.cell_nodes), st, f,
-                         (const int32_t*)S.tile_inv, a);
-    else
-      hipLaunchKernelGGL(shape_cell_kernel<false>, dim3(nc), dim3(64 * kFieldWaves), 0, st, f,
-                         (const int32_t*)S.tile_inv, a);
+    // The helpers beside the cells' workgroups cost no launch (1.5 to 2 us), but give
+    // all of those the LDS of the search: only if they fit the chip with it at once.
+    const int help = S.n_helpers;
+    const size_t search = cell_lds(S.cell_nodes);
+    if (help > 0 && nc <= 256 * (int)(163840 / (search + 512))) {
+      hipLaunchKernelGGL(shape_cell_kernel<true>, dim3(nc + help), dim3(64 * kFieldWaves),
+                         search, st, f, (const int32_t*)S.tile_inv, a);
+      return hipGetLastError();
+    }
+    if (help > 0) {
+      hipLaunchKernelGGL(shape_help_kernel, dim3(help), dim3(64 * kFieldWaves), search, st,
+                         f, a);
+      if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(shape_cell_kernel<false>, dim3(nc), dim3(64 * kFieldWaves), 0, st, f,
+                       (const int32_t*)S.tile_inv, a);
     return hipGetLastError();
   }
   if (mom_blocks > 0) {

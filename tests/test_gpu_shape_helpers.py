@@ -92,6 +92,23 @@ def test_uneven_cells_again_and_again():
     assert np.array_equal(outs[0], outs[1]) and np.array_equal(outs[0], outs[2])
 
 
+@pytest.mark.parametrize("small", [300, 1000])
+def test_large_cells_among_many(small):
+    """Two large spheres among many small cells, for which the shared search has a
+    launch of its own or goes beside the cells' fields."""
+    from paper_2003_03130_amd import CellBatch
+    stars = [_star(20)] * (small // 2) + [_star(3700)] + [_star(20)] * (small // 2) + [_star(2500)]
+    off = np.concatenate([[0], np.cumsum([len(x) for x, _ in stars])])
+    toff = np.concatenate([[0], np.cumsum([len(t) for _, t in stars])])
+    x = np.concatenate([s[0] for s in stars])
+    cb = CellBatch(off, toff, x, np.concatenate([s[1] for s in stars]))
+    for f in ([1, 1, 1], [1.3, 1, 0.9]):
+        y = (x * f).astype(np.float32)
+        out = cb.shape(cb.to_device(y), 2.0).cpu().numpy()
+        for k in (0, small // 2, small // 2 + 1, len(stars) - 1):
+            _same(out[k, 8], _d_max(y[off[k]:off[k + 1]]))
+
+
 def test_inverted_and_non_finite():
     from paper_2003_03130_amd import CellBatch
     x, tets = _star(800)
