@@ -12,6 +12,7 @@
 #include "aux_kernels.h"
 #include "cellmech.h"
 #include "kernels.h"
+#include "shape.h"
 
 namespace cm {
 

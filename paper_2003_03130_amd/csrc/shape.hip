@@ -57,7 +57,7 @@
 #include <cmath>
 
 #include "device_util.h"
-#include "aux_kernels.h"
+#include "shape.h"
 
 namespace cm {
 namespace {
@@ -691,7 +691,7 @@ __device__ __forceinline__ void search_pairs(const CellArgs& a, float* sx, int k
 }
 
 // The search of cell c by one workgroup; where too many nodes remain for it
-// (search_helpers, aux_kernels.h), only up to them: a.rest is for the helpers.
+// (search_helpers, shape.h), only up to them: a.rest is for the helpers.
 template <int W>
 __device__ __forceinline__ void cell_search(const CellArgs& a, int c, float* sx) {
   __shared__ double rv[W];
