@@ -18,19 +18,22 @@ constexpr int kShapeFields = 10;
 // LDS (with their boxes 55 KB).
 constexpr int kCellNodes = 4096;
 
-// The workgroup that searches a cell compares alone the pairs of up to kSearchNodes
-// remaining nodes, or of an eighth of the candidates if that is more; those of more
-// (near-spherical cells, where all remain) it leaves to helpers, up to 32 further
-// workgroups of the cell: of 1,024 its share by the square of its candidates, none
-// if that is below four (many cells of one size, whose searches fill the chip, and
-// the small ones beside large ones).
-// Equal spheres, alone -> with helpers, and by the block search: 1 cell of 2,000
-// nodes 47 -> 22 us (46), of 9,000 185 -> 41 (54), of 20,000 334 -> 64 (68); 64 cells
-// of 2,000 48 -> 25 (58), of 20,000 343 -> 158 (222); 256 of 9,000 197 -> 173 (259).
-// Ellipsoids, of which a few nodes remain, pay 0.1 to 0.5 us of 14 to 37.  The line:
-// noisy spheres with 250 to 500 nodes left, 64 cells of 2,000 nodes 43 alone, 26
-// shared; but with 293 of 3,670 candidates left, which every helper loads again, 64
-// cells of 20,000 nodes 41 alone, 60 shared.
+// The workgroup that searches a cell of up to kSearchAlone candidates compares the
+// remaining nodes' pairs alone: so it takes no longer than the block search did even
+// for a sphere, of which all remain (1 cell of 2,000 nodes 45 us, 46 by that).  In
+// larger cells it does so for up to kSearchNodes remaining nodes, or an eighth of the
+// candidates if that is more, and leaves the pairs of more of them to helpers, up to 32
+// further workgroups of the cell: of 1,024 its share by the square of its candidates,
+// none if that is below four (many cells of one size, whose searches fill the chip,
+// and the small ones beside large ones).
+// Equal spheres, alone -> with helpers, and by the block search: 1 cell of 3,800 nodes
+// 87 -> 26 us (49), of 9,000 185 -> 41 (54), of 20,000 334 -> 63 (68); 64 cells of 9,000
+// 190 -> 72 (110), of 20,000 343 -> 156 (222); 256 of 9,000 197 -> 173 (259).
+// Ellipsoids, of which a few nodes remain, pay 0.1 to 0.4 us of 15 to 53.  The line of
+// kSearchNodes: noisy spheres with 250 to 500 nodes left, 64 cells of 2,000 nodes 43
+// alone, 26 shared; but with 293 of 3,670 candidates left, which every helper loads
+// again, 64 cells of 20,000 nodes 41 alone, 60 shared.
+constexpr int kSearchAlone = 768;
 constexpr int kSearchNodes = 256;
 
 // Helpers of every cell and, a pair for each of them, the cell and the helper's
@@ -44,7 +47,7 @@ inline void search_helpers(const std::vector<int32_t>& candidates,
   for (size_t c = 0; c < candidates.size(); ++c) {
     const double n = candidates[c];
     const int share = (int)std::min(32.0, 1024.0 * n * n / all);
-    if (candidates[c] <= kSearchNodes || share < 4) continue;
+    if (candidates[c] <= kSearchAlone || share < 4) continue;
     (*helpers)[c] = share;
     cells.push_back((int32_t)c);
   }
@@ -59,7 +62,7 @@ inline void search_helpers(const std::vector<int32_t>& candidates,
 struct alignas(64) SearchRest {
   double centre[3], least2;
   int32_t left;   // to how many helpers (0: the search is done)
-  uint32_t done;  // workgroups of the cell that have arrived
+  uint32_t done;  // helpers of the cell that have arrived
 };
 
 // Tables and scratch of a handle's shape diagnostics.  cell_nodes: the

@@ -747,15 +747,19 @@ __device__ __forceinline__ void cell_search(const CellArgs& a, int c, float* sx)
   const int kept = keep_far_nodes<W>(a, ns, sx, cx, cy, cz, least2, ri);
   if (a.rest) {
     const int helpers = a.helpers[c];
-    const bool leave = helpers > 0 && kept > max(kSearchNodes, ns / 8);
-    if (tid == 0) a.rest[c] = SearchRest{{cx, cy, cz}, least2, leave ? helpers : 0, 0};
-    if (leave) {
-      if (tid == 0) a.d2max[c] = (unsigned long long)__double_as_longlong(L2);
+    if (helpers > 0 && kept > max(kSearchNodes, ns / 8)) {
+      if (tid == 0) {
+        a.rest[c] = SearchRest{{cx, cy, cz}, least2, helpers, 0};
+        a.d2max[c] = (unsigned long long)__double_as_longlong(L2);
+      }
       return;
     }
   }
   search_pairs<W>(a, sx, kept, L2, 0, W, &best_bits);
-  if (tid == 0) a.d2max[c] = best_bits;
+  if (tid == 0) {
+    a.d2max[c] = best_bits;
+    if (a.rest) a.rest[c].left = 0;
+  }
 }
 
 // The searches, one workgroup per cell, and behind them in the same launch the
@@ -782,10 +786,21 @@ __global__ __launch_bounds__(64 * W) void shape_pass_kernel(CellArgs a) {
     tile_moments(a.mom, (int)t, lane, lds + (size_t)wave * a.mom.T.nloc);
 }
 
-// A helper of cell c: it loads the candidates again, keeps the same nodes and takes
-// its share of their pairs; with LAST, the last of the cell's workgroups to arrive
-// writes the distance.
 constexpr int kFieldWaves = 4;
+
+// Whether a tetrahedron of cell c is not positively oriented: this thread's part.
+__device__ __forceinline__ int cell_inverted(const ShapeFinArgs& f, const int32_t* tile_inv,
+                                             int c, int tid) {
+  int inv = 0;
+  const int t0 = f.T.cell_tile_first[c], nt = f.T.cell_tile_count[c];
+  for (int k = tid; k < nt; k += 64 * kFieldWaves)
+    inv |= tile_inv[t0 + (int64_t)k * f.T.tile_stride];
+  return inv;
+}
+
+// A helper of cell c: it loads the candidates again, keeps the same nodes and takes
+// its share of their pairs; with LAST, the last of the cell's helpers to arrive
+// writes the distance.
 
 template <bool LAST>
 __device__ __forceinline__ void help_search(const ShapeFinArgs& f, const CellArgs& a, int c,
@@ -806,7 +821,9 @@ __device__ __forceinline__ void help_search(const ShapeFinArgs& f, const CellArg
                             kFieldWaves * helper, kFieldWaves * r.left, &best_bits);
   if (tid == 0 && best_bits > start) atomicMax(a.d2max + c, best_bits);
   if constexpr (LAST) {
-    if (last_arrival(&a.rest[c].done, r.left, tid, &flag) && tid == 0)
+    if (!last_arrival(&a.rest[c].done, r.left - 1, tid, &flag)) return;
+    // (a cell with an inverted tetrahedron: all its pairs were compared elsewhere)
+    if (!__syncthreads_or(cell_inverted(f, a.mom.tile_inv, c, tid)) && tid == 0)
       shape_distance(f, c, __longlong_as_double((long long)device_load(a.d2max + c)));
   }
 }
@@ -822,38 +839,30 @@ __global__ __launch_bounds__(64 * kFieldWaves) void shape_help_kernel(ShapeFinAr
 // The cell's fields, by one wavefront; all four search all node pairs first if
 // the cell has a tetrahedron that is not positively oriented, which the
 // candidates do not cover.  HELP: behind the cells' workgroups, the helpers of
-// each.
+// each, which write the distance of a cell whose search was left to them, unless
+// all its pairs are compared here.
 template <bool HELP>
 __global__ __launch_bounds__(64 * kFieldWaves) void shape_cell_kernel(ShapeFinArgs f,
                                                                       const int32_t* tile_inv,
                                                                       CellArgs a) {
   extern __shared__ float4 lds[];
   __shared__ double rv[kFieldWaves];
-  __shared__ int flag;
   const int c = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
   if (!HELP || c < f.T.n_cells) {
-    int inv = 0;
-    {
-      const int t0 = f.T.cell_tile_first[c], nt = f.T.cell_tile_count[c];
-      for (int k = tid; k < nt; k += 64 * kFieldWaves)
-        inv |= tile_inv[t0 + (int64_t)k * f.T.tile_stride];
-    }
-    const int left = HELP ? a.rest[c].left : 0;
+    const int inv = cell_inverted(f, tile_inv, c, tid);
+    // (the helpers raise d2max meanwhile)
+    const bool left = HELP && a.rest[c].left != 0;
     double d2 = left ? 0.0 : __longlong_as_double((long long)f.d2max[c]);
-    if (__syncthreads_or(inv != 0)) {
+    const bool all = __syncthreads_or(inv != 0);
+    if (all) {
       const double m = wave_max(all_pairs(f.y, f.T.n_nodes, f.node_off[c], f.node_off[c + 1]));
       if (lane == 0) rv[tid >> 6] = m;
       __syncthreads();
       d2 = fmax(fmax(d2, fmax(rv[0], rv[1])), fmax(rv[2], rv[3]));
     }
-    if (tid < 64) shape_fields(f, c, lane);
-    if (left) {
-      if (tid == 0 && d2 > 0.0)
-        atomicMax(a.d2max + c, (unsigned long long)__double_as_longlong(d2));
-      if (!last_arrival(&a.rest[c].done, left, tid, &flag)) return;
-      d2 = __longlong_as_double((long long)device_load(a.d2max + c));
-    }
-    if (tid == 0) shape_distance(f, c, d2);
+    if (tid >= 64) return;
+    shape_fields(f, c, lane);
+    if (lane == 0 && (!left || all)) shape_distance(f, c, d2);
     return;
   }
   if constexpr (HELP) {

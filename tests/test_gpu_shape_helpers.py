@@ -43,7 +43,7 @@ def _same(a, b):
 
 
 @pytest.mark.parametrize("cells", [1, 3, 256, 257])
-@pytest.mark.parametrize("surface", [255, 256, 257, 700])
+@pytest.mark.parametrize("surface", [300, 768, 769, 1500])
 def test_spheres(surface, cells):
     from paper_2003_03130_amd import CellBatch
     x, tets = _star(surface)
@@ -55,6 +55,11 @@ def test_spheres(surface, cells):
         _same(out[k, 8], _d_max(y[k]))
         assert abs(out[k, 9] - (out[k, 8] - 2.0) / 2.0) <= 1e-15
         assert np.array_equal(out[k::5, 8], np.full(len(out[k::5]), out[k, 8]))
+    # rings of a few nodes to most of them remain
+    y[:, :, 2] *= np.linspace(0.95, 1.0, cells, dtype=np.float32)[:, None]
+    out = cb.shape(cb.to_device(y.reshape(-1, 3)), 2.0).cpu().numpy()
+    for k in np.unique(np.linspace(0, cells - 1, 12).astype(int)):
+        _same(out[k, 8], _d_max(y[k]))
 
 
 @pytest.mark.parametrize("cells", [1, 40])
